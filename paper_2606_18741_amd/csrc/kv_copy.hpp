@@ -56,10 +56,11 @@ __global__ __launch_bounds__(kMaxRunThreads) void copy_runs(const CopyArgs<ITEMS
 // Local copy (a slice whose old and new owner is the same rank): the new pool's live blocks are walked as
 // in copy_runs, and each row's source is found through the old descriptors.  A new block's first token
 // lies t0 tokens into its sequence, whose old blocks start at descriptor b0; both come by scalar loads
-// behind the block's own descriptor.  With one block size on both sides (SAME) the old descriptor is a
-// third scalar load; else each lane loads its row's.  Bound by HBM: the chain of scalar loads costs 2%
-// (MI355X, 4 KiB blocks: 6.12 TB/s against 6.24 with the old block ids at hand), where the rows of
-// 16 KiB of units resolved into LDS before the copy, by 256 threads x 2 vectors, ran at 5.5.
+// behind the block's own descriptor, and behind them the M old descriptors that the wave's rows of the block can come
+// from.  Where those are more than two, or the wave meets many blocks, each lane loads its row's (M = 0, N = 0).
+// Bound by HBM.  Measured on MI355X: the chain of scalar loads costs 2% (4 KiB blocks 6.12 TB/s, 6.24 with the old
+// block ids at hand); the rows of 16 KiB resolved into LDS first, by 256 threads x 2 vectors, ran at 5.5, and a look-up
+// per lane between block sizes at 4.9 (256-byte rows, blocks of 64 to 20, us: LDS 652, by lane 713, so 620).
 constexpr int kMaxLocalItems = 8;     // local slices per launch (few per launch measured faster, as for kMaxItems)
 constexpr int kMaxLocalRows = 1024;   // largest new block size of the local copies
 
@@ -92,117 +93,169 @@ struct LocalArgs {
 };
 static_assert(sizeof(LocalArgs) < 4096, "local copy kernel arguments must stay below 4 KiB");
 
-// What the lanes of a wave need to know of one new block: its descriptor, its first token's index in its
-// sequence (negative when the device tables disagree), the sequence's first old descriptor and, with
-// SAME, the old block that holds its rows slot for slot (n = 0: resolve row by row).
-struct LocalUnit {
-    BlockDesc d;
-    int32_t t0, b0;
+// What the lanes of a wave need to know of one new block: its id, live tokens and sequence, its first token's index in its
+// sequence (negative when the device tables disagree), the sequence's first old descriptor and the M (0: none) old
+// blocks from number b0 + q on that hold its rows from `row` on, as (id, live tokens; 0: not of this sequence).
+struct OldBlock {
     int32_t block, n;
 };
 
-template <bool SAME, typename Args, typename Table, typename Ints>
-__device__ __forceinline__ LocalUnit load_local_unit(const Args& a, const Table* new_desc, const Table* old_desc,
-                                                     const Ints* tok_off, const Ints* blk_off, uint32_t u) {
-    const auto v = new_desc[u];
-    LocalUnit x;
-    x.d = BlockDesc{v.x, v.y, v.z, v.w};
-    x.t0 = x.d.tok - tok_off[x.d.seq];
-    x.b0 = blk_off[x.d.seq];
-    x.block = 0;
-    x.n = 0;
-    if (SAME && x.t0 >= 0) {
-        const uint32_t q = fast_div(static_cast<uint32_t>(x.t0), a.bo_magic, a.bo_shift);
-        const int64_t ob = static_cast<int64_t>(x.b0) + q;
-        if (q * a.old_block_size == static_cast<uint32_t>(x.t0) && ob >= 0 && ob < a.n_old_desc) {
-            const auto o = old_desc[ob];
-            x.block = o.x;
-            x.n = o.w == x.d.seq ? o.z : 0;
-        }
+template <int M>
+struct LocalUnit {
+    int32_t block, n, seq;
+    int32_t t0, b0;
+    uint32_t q;
+    Values<OldBlock, M> o;
+};
+
+__device__ __forceinline__ void choose(bool yes, const OldBlock& v, OldBlock* own) {
+    own->block = yes ? v.block : own->block;
+    own->n = yes ? v.n : own->n;
+}
+
+template <typename T>
+__device__ __forceinline__ void choose(bool, const Values<T, 0>&, Values<T, 0>*) {}
+
+template <typename T, int N>
+__device__ __forceinline__ void choose(bool yes, const Values<T, N>& v, Values<T, N>* own) {
+    choose(yes, v.v, &own->v);
+    choose(yes, v.next, &own->next);
+}
+
+template <int M>
+__device__ __forceinline__ void choose(bool yes, const LocalUnit<M>& v, LocalUnit<M>* own) {
+    own->block = yes ? v.block : own->block;
+    own->n = yes ? v.n : own->n;
+    own->seq = yes ? v.seq : own->seq;
+    own->t0 = yes ? v.t0 : own->t0;
+    own->b0 = yes ? v.b0 : own->b0;
+    own->q = yes ? v.q : own->q;
+    choose(yes, v.o, &own->o);
+}
+
+template <int M, typename Args, typename Table, typename Ints>
+__device__ __forceinline__ LocalUnit<M> load_local_unit(const Args& a, const Table* new_desc, const Table* old_desc,
+                                                        const Ints* tok_off, const Ints* blk_off, uint32_t u,
+                                                        uint32_t row) {
+    const Int4 v = new_desc[u];
+    LocalUnit<M> x;
+    x.block = v.x;
+    x.n = v.z;
+    x.seq = v.w;
+    x.t0 = v.y - tok_off[v.w];
+    x.b0 = blk_off[v.w];
+    x.q = 0;
+    if (M) {
+        const int64_t t = static_cast<int64_t>(x.t0) + row;
+        x.q = fast_div(static_cast<uint32_t>(t < 0 ? 0 : t), a.bo_magic, a.bo_shift);
     }
+    x.o.fill([&](uint32_t m) {
+        const int64_t b = static_cast<int64_t>(x.b0) + x.q + m;
+        const bool in = b >= 0 && b < a.n_old_desc;
+        const Int4 o = old_desc[in ? b : 0];
+        return OldBlock{o.x, in && o.w == v.w ? o.z : 0};
+    });
     return x;
 }
 
-// V: bytes that a lane moves, 16, 8 or 4 aligned ones, or 0: 16 at any address and a row's last part in smaller ones.
-template <int N, bool SAME, int V>
+// Old block and slot of a row of the unit; false when it has no source.
+template <int M, typename Args>
+__device__ __forceinline__ bool find_source(const Args& a, const LocalUnit<M>& x, uint32_t row, int32_t* block,
+                                            uint32_t* slot) {
+    // token within its sequence: the new expansion's token offset less the old one's, so device tables
+    // that disagree can make it negative; such a row has no source
+    const int32_t t = x.t0 + static_cast<int32_t>(row);
+    if (t < 0) return false;
+    uint32_t s = static_cast<uint32_t>(t) - x.q * a.old_block_size, passed = 0;
+    OldBlock o;
+    if constexpr (M > 0) {
+        o = x.o.v;
+        x.o.next.advance(a.old_block_size, &s, &passed, &o);
+    }
+    if (M == 0 || s >= a.old_block_size) {   // with M: only where the device tables disagree about the sequence's start
+        const uint32_t q = fast_div(static_cast<uint32_t>(t), a.bo_magic, a.bo_shift);
+        const int64_t ob = static_cast<int64_t>(x.b0) + q;
+        if (ob < 0 || ob >= a.n_old_desc) return false;
+        s = static_cast<uint32_t>(t) - q * a.old_block_size;
+        const BlockDesc d = a.old_desc[ob];
+        o = OldBlock{d.block, d.seq == x.seq ? d.n : 0};
+    }
+    *slot = s;
+    *block = o.block;
+    return s < static_cast<uint32_t>(o.n);
+}
+
+template <int N, int M, int V, int K>
 __global__ __launch_bounds__(kMaxRunThreads) void copy_local(const LocalArgs args) {
-    typedef int Int4 __attribute__((ext_vector_type(4)));
+    constexpr uint32_t W = V ? V : kVecBytes;   // bytes of a word
     if (stale_descriptors(args.check)) return;
     const LocalItem& it = args.items[blockIdx.y];
-    const uint32_t kv = blockIdx.z, w0 = wave_first(args.xcd), lane = threadIdx.x & 63u, vpu = it.vpu;
-    LocalUnit x;
-    uint32_t r;
-    if (N == 0) {   // as in pick_unit: small units, every lane by itself
-        const uint32_t u = fast_div(w0 + lane, it.vpu_magic, it.vpu_shift);
-        if (u >= args.n_new_desc) return;
-        r = w0 + lane - u * vpu;
-        x = load_local_unit<SAME>(args, reinterpret_cast<const Int4*>(args.new_desc),
-                                  reinterpret_cast<const Int4*>(args.old_desc), args.tok_off, args.old_blk_off, u);
-    } else {
+    const uint32_t kv = blockIdx.z, w0 = wave_first(args.xcd) * K, lane = threadIdx.x & 63u, vpu = it.vpu;
+    const uint32_t vpr = (it.row_bytes + W - 1) / W;
+    Values<LocalUnit<M>, N> units;
+    uint32_t u0 = 0;
+    if constexpr (N > 0) {
         const REMP_CONSTANT Int4* nd = (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(args.new_desc));
         const REMP_CONSTANT Int4* od = (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(args.old_desc));
         const REMP_CONSTANT int32_t* to = (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(args.tok_off));
         const REMP_CONSTANT int32_t* bo = (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(args.old_blk_off));
-        const uint32_t u0 = fast_div(w0, it.vpu_magic, it.vpu_shift);
+        u0 = fast_div(w0, it.vpu_magic, it.vpu_shift);
         if (u0 >= args.n_new_desc) return;
-        uint32_t u = u0;
-        r = w0 - u0 * vpu + lane;
-        x = load_local_unit<SAME>(args, nd, od, to, bo, u0);
+        const uint32_t row = M ? fast_div(w0 - u0 * vpu, it.vpr_magic, it.vpr_shift) : 0;
+        units.fill([&](uint32_t k) {
+            return load_local_unit<M>(args, nd, od, to, bo, min(u0 + k, args.n_new_desc - 1), k ? 0 : row);
+        });
+    }
+    LocalUnit<M> own[K];
+    uint32_t at[K];
+    bool in[K];
 #pragma unroll
-        for (int k = 1; k < N; ++k) {
-            const LocalUnit next = load_local_unit<SAME>(args, nd, od, to, bo, min(u0 + k, args.n_new_desc - 1));
-            if (r >= vpu) {
-                r -= vpu;
-                u = u0 + k;
-                x = next;
-            }
+    for (int k = 0; k < K; ++k) {
+        if constexpr (N == 0) {   // as in pick_unit: small units, every lane by itself
+            const uint32_t w = w0 + k * 64 + lane, u = fast_div(w, it.vpu_magic, it.vpu_shift);
+            in[k] = u < args.n_new_desc;
+            at[k] = w - u * vpu;
+            own[k] = load_local_unit<M>(args, reinterpret_cast<const Int4*>(args.new_desc),
+                                        reinterpret_cast<const Int4*>(args.old_desc), args.tok_off, args.old_blk_off,
+                                        min(u, args.n_new_desc - 1), fast_div(at[k], it.vpr_magic, it.vpr_shift));
+        } else {
+            uint32_t u = u0;
+            at[k] = w0 - u0 * vpu + k * 64 + lane;
+            own[k] = units.v;
+            units.next.advance(vpu, &at[k], &u, &own[k]);
+            in[k] = u < args.n_new_desc;
         }
-        if (u >= args.n_new_desc) return;
     }
-
-    constexpr uint32_t vec = V ? V : kVecBytes;
-    const uint32_t vpr = (it.row_bytes + vec - 1) / vec;
-    const uint32_t row = fast_div(r, it.vpr_magic, it.vpr_shift);
-    if (row >= static_cast<uint32_t>(x.d.n)) return;
-    int32_t block = x.block;
-    uint32_t slot = row;
-    if (!SAME || row >= static_cast<uint32_t>(x.n)) {
-        // token within its sequence: the new expansion's token offset less the old one's, so device tables
-        // that disagree can make it negative; such a row has no source
-        const int32_t t = x.t0 + static_cast<int32_t>(row);
-        bool ok = t >= 0;
-        if (ok) {
-            const uint32_t q = fast_div(static_cast<uint32_t>(t), args.bo_magic, args.bo_shift);
-            const int64_t ob = static_cast<int64_t>(x.b0) + q;
-            slot = static_cast<uint32_t>(t) - q * args.old_block_size;
-            ok = ob >= 0 && ob < args.n_old_desc;
-            if (ok) {
-                const BlockDesc o = args.old_desc[ob];
-                ok = o.seq == x.d.seq && slot < static_cast<uint32_t>(o.n);
-                block = o.block;
-            }
-        }
-        if (!ok) {
+    Moved<V> word[K];
+    uint64_t dst[K];
+    uint32_t left[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        left[k] = 0;
+        if (!in[k]) continue;
+        const LocalUnit<M>& x = own[k];
+        const uint32_t r = at[k];
+        const uint32_t row = fast_div(r, it.vpr_magic, it.vpr_shift);
+        if (row >= static_cast<uint32_t>(x.n)) continue;
+        int32_t block;
+        uint32_t slot;
+        if (!find_source(args, x, row, &block, &slot)) {
             *args.flag = kFlagTables;
-            return;
+            continue;
         }
+        const uint32_t off = (r - row * vpr) * W;
+        const uint64_t src = (kv ? it.src_v : it.src_k) +
+                             static_cast<uint64_t>(static_cast<uint32_t>(block)) * static_cast<uint64_t>(args.old_block_stride) +
+                             static_cast<uint64_t>(slot) * args.old_row_stride + off;
+        dst[k] = (kv ? it.dst_v : it.dst_k) +
+                 static_cast<uint64_t>(static_cast<uint32_t>(x.block)) * static_cast<uint64_t>(args.new_block_stride) +
+                 static_cast<uint64_t>(row) * args.new_row_stride + off;
+        left[k] = it.row_bytes - off;
+        word[k].load(src, left[k]);
     }
-    const uint64_t src = (kv ? it.src_v : it.src_k) +
-                         static_cast<uint64_t>(static_cast<uint32_t>(block)) * static_cast<uint64_t>(args.old_block_stride) +
-                         static_cast<uint64_t>(slot) * args.old_row_stride;
-    const uint64_t dst = (kv ? it.dst_v : it.dst_k) +
-                         static_cast<uint64_t>(static_cast<uint32_t>(x.d.block)) * static_cast<uint64_t>(args.new_block_stride) +
-                         static_cast<uint64_t>(row) * args.new_row_stride;
-    const uint32_t off = (r - row * vpr) * vec;
-    if (V == 8) {
-        const uint64_t v = __builtin_nontemporal_load((const REMP_GLOBAL uint64_t*)(src + off));
-        __builtin_nontemporal_store(v, (REMP_GLOBAL uint64_t*)(dst + off));
-    } else if (V == 4) {
-        const uint32_t v = __builtin_nontemporal_load((const REMP_GLOBAL uint32_t*)(src + off));
-        __builtin_nontemporal_store(v, (REMP_GLOBAL uint32_t*)(dst + off));
-    } else {
-        move_vector<V == 0>(src, dst, off, it.row_bytes);
-    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (left[k]) word[k].store(dst[k], left[k]);
 }
 
 }  // namespace remp

@@ -89,6 +89,12 @@ constexpr int kRunThreads = 64;
 constexpr int kRowsPackThreads = 256;
 constexpr int kMaxRunThreads = 1024;   // the most the tuning override asks for
 constexpr int kScanThreads = 1024;
+// Rows that are not whole vectors go by 8-byte words up to these bytes, where they are aligned to that.
+constexpr uint32_t kLocalWordRow = 512;
+// Such words of a lane: 2 (1 KiB to a wave), and 4 in the local copy where a block has as many, so that its look-ups serve
+// more bytes (MI355X, us, 2 / 4 words: 200-byte rows in blocks of 64 718 / 666, blocks of 64 to 20 706 / 672; but of 72
+// bytes, blocks of 32 to 16, 897 / 1100).
+constexpr int kLocalWords = 4;
 
 struct CopyItem {
     uint64_t paged_k;     // K storage of the layer, offset to the slice's first head
@@ -102,48 +108,103 @@ struct CopyItem {
     uint16_t vpu_shift;
 };
 
-// The unit (live block, K or V) that a lane works on.  The vectors of a slice's units are numbered unit
-// after unit, `vpu` to a unit, and a wave takes 64 consecutive ones from w0 (the same for all its
-// lanes), so it meets the few units unit(w0), unit(w0) + 1, ...: their descriptors come by scalar
-// loads, and each lane keeps the one its vector falls into.  N bounds the units a wave can meet
+// The unit (live block, K or V) that a lane works on.  The words of a slice's units (16-byte vectors, or words of 8 or 4
+// bytes) are numbered unit after unit, `vpu` to a unit, and a wave takes 1 KiB of consecutive ones from w0 (the same
+// for all its lanes), so it meets the few units unit(w0), unit(w0) + 1, ...: their descriptors come by scalar
+// loads, and each lane keeps the one its word falls into.  N bounds the units a wave can meet
 // (units_per_wave); N == 0 means any number, each lane loading its own descriptor.  Per-lane loads
 // cost 15% of the copy (MI355X, 4 KiB units: 5.30 against 6.29 TB/s), so they are left to units of less than
-// 128 bytes.  False when the lane is past the last unit.
+// 128 bytes.
+typedef int Int4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void choose(bool yes, const Int4& v, Int4* own) { *own = yes ? v : *own; }
+
+// N values in registers.  Not an array: a lane's choice among an array's elements is compiled to an indexed access, for
+// which the array goes to LDS or scratch.
+template <typename T, int N>
+struct Values {
+    T v;
+    Values<T, N - 1> next;
+
+    template <typename F>
+    __device__ __forceinline__ void fill(const F& f, uint32_t k = 0) {
+        v = f(k);
+        next.fill(f, k + 1);
+    }
+    // Moves *own on by one value for every `size` that fits into *x.
+    __device__ __forceinline__ void advance(uint32_t size, uint32_t* x, uint32_t* passed, T* own) const {
+        const bool past = *x >= size;
+        const T mine = v;
+        *x -= past ? size : 0;
+        *passed += past;
+        choose(past, mine, own);
+        next.advance(size, x, passed, own);
+    }
+};
+
+template <typename T>
+struct Values<T, 0> {
+    template <typename F>
+    __device__ __forceinline__ void fill(const F&, uint32_t = 0) {}
+    __device__ __forceinline__ void advance(uint32_t, uint32_t*, uint32_t*, T*) const {}
+};
+
+template <int N>
+struct WaveUnits {
+    Values<Int4, N> v;
+    uint32_t w0, u0, r0;   // the wave's first word, its unit and its position there
+
+    // False when the wave lies past the last unit.
+    __device__ __forceinline__ bool load(const BlockDesc* desc, uint32_t n_desc, uint32_t first, uint32_t vpu,
+                                         uint32_t magic, uint32_t shift) {
+        w0 = first;
+        if constexpr (N > 0) {
+            u0 = fast_div(w0, magic, shift);
+            if (u0 >= n_desc) return false;
+            r0 = w0 - u0 * vpu;
+            const REMP_CONSTANT Int4* table = (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(desc));
+            v.fill([&](uint32_t k) { return table[min(u0 + k, n_desc - 1)]; });
+        }
+        return true;
+    }
+
+    // Descriptor of the wave's i-th word and its position r in its unit; false past the last unit.
+    __device__ __forceinline__ bool pick(const BlockDesc* desc, uint32_t n_desc, uint32_t i, uint32_t vpu,
+                                         uint32_t magic, uint32_t shift, BlockDesc* d, uint32_t* r) const {
+        if constexpr (N == 0) {
+            const uint32_t u = fast_div(w0 + i, magic, shift);
+            if (u >= n_desc) return false;
+            *r = w0 + i - u * vpu;
+            *d = desc[u];
+            return true;
+        } else {
+            uint32_t u = u0;
+            *r = r0 + i;
+            Int4 own = v.v;
+            v.next.advance(vpu, r, &u, &own);
+            *d = BlockDesc{own.x, own.y, own.z, own.w};
+            return u < n_desc;
+        }
+    }
+};
+
 template <int N>
 __device__ __forceinline__ bool pick_unit(const BlockDesc* desc, uint32_t n_desc, uint32_t w0, uint32_t lane,
                                           uint32_t vpu, uint32_t magic, uint32_t shift, BlockDesc* d, uint32_t* r) {
-    typedef int Int4 __attribute__((ext_vector_type(4)));
-    if (N == 0) {
-        const uint32_t i = w0 + lane;
-        const uint32_t u = fast_div(i, magic, shift);
-        if (u >= n_desc) return false;
-        *r = i - u * vpu;
-        *d = desc[u];
-        return true;
-    }
-    const uint32_t u0 = fast_div(w0, magic, shift);
-    if (u0 >= n_desc) return false;
-    uint32_t u = u0, x = w0 - u0 * vpu + lane;
-    const REMP_CONSTANT Int4* table = (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(desc));
-    Int4 v = table[u0];
-#pragma unroll
-    for (int k = 1; k < N; ++k) {
-        const Int4 next = table[min(u0 + k, n_desc - 1)];
-        if (x >= vpu) {
-            x -= vpu;
-            u = u0 + k;
-            v = next;
-        }
-    }
-    *d = BlockDesc{v.x, v.y, v.z, v.w};
-    *r = x;
-    return u < n_desc;
+    WaveUnits<N> units;
+    return units.load(desc, n_desc, w0, vpu, magic, shift) &&
+           units.pick(desc, n_desc, lane, vpu, magic, shift, d, r);
 }
 
-// Units that 64 consecutive vectors can touch when a unit has vpu of them, as the template argument of
-// pick_unit: 1, 2, 4 or 8, and 0 beyond 8.
-inline int units_per_wave(uint32_t vpu) {
-    const uint32_t most = vpu % 64 == 0 ? 1 : 64 % vpu == 0 ? 64 / vpu : 62 / vpu + 2;
+// Pieces of `size` words, one after another, that the `wave` consecutive words of a wave can touch; waves begin at multiples of
+// `wave`, pieces at multiples of `size`.
+inline uint32_t pieces_per_wave(uint32_t size, uint32_t wave) {
+    return size % wave == 0 ? 1 : wave % size == 0 ? wave / size : (wave - 2) / size + 2;
+}
+
+// The same for units of vpu words, as the template argument of pick_unit: 1, 2, 4 or 8, and 0 beyond 8.
+inline int units_per_wave(uint32_t vpu, uint32_t wave = 64) {
+    const uint32_t most = pieces_per_wave(vpu, wave);
     return most <= 1 ? 1 : most <= 2 ? 2 : most <= 4 ? 4 : most <= 8 ? 8 : 0;
 }
 
@@ -166,38 +227,64 @@ __device__ __forceinline__ uint32_t wave_first(uint32_t xcd) {
         __builtin_amdgcn_readfirstlane(static_cast<int>((wg * blockDim.x + threadIdx.x) & ~63u)));
 }
 
-// Move bytes [off, off + 16) of a run of `len` bytes; the last vector of a run whose length is not a
-// multiple of 16 moves only what is left, in parts of 8, 4, 2 and 1 bytes.  ODD: the run may have any length
-// and any alignment (hardware takes unaligned global vectors).
-template <bool ODD>
-__device__ __forceinline__ void move_vector(uint64_t src, uint64_t dst, uint32_t off, uint32_t len) {
-    if (!ODD) {
-        const Vec16 v = __builtin_nontemporal_load((const REMP_GLOBAL Vec16*)(src + off));
-        __builtin_nontemporal_store(v, (REMP_GLOBAL Vec16*)(dst + off));
-        return;
+// What one lane moves at a time, held in registers: a word of V (16, 8 or 4) bytes at an aligned address, or (V == 0) at
+// most 16 bytes at any address (hardware takes unaligned global vectors): fewer, in parts of 8, 4, 2 and 1, where a
+// run ends.  `left`: bytes of the run from here on.  Callers load all they move before they store any of it: a
+// part that was stored before the next was loaded cost a wave a second trip to memory.
+template <int V>
+struct Moved {
+    typedef typename VecT<V>::type Word;
+    Word w;
+
+    __device__ __forceinline__ void load(uint64_t src, uint32_t) {
+        w = __builtin_nontemporal_load((const REMP_GLOBAL Word*)src);
     }
-    if (off + kVecBytes <= len) {
-        const Vec16Any v = __builtin_nontemporal_load((const REMP_GLOBAL Vec16Any*)(src + off));
-        __builtin_nontemporal_store(v, (REMP_GLOBAL Vec16Any*)(dst + off));
-        return;
+    __device__ __forceinline__ void store(uint64_t dst, uint32_t) const {
+        __builtin_nontemporal_store(w, (REMP_GLOBAL Word*)dst);
     }
+};
+
+template <>
+struct Moved<0> {
     typedef uint64_t Part8 __attribute__((aligned(1)));
     typedef uint32_t Part4 __attribute__((aligned(1)));
     typedef uint16_t Part2 __attribute__((aligned(1)));
-    const uint32_t rest = len - off;
-    const uint32_t at4 = off + (rest & 8u), at2 = at4 + (rest & 4u), at1 = at2 + (rest & 2u);
-    uint64_t p8 = 0;
-    uint32_t p4 = 0;
-    uint16_t p2 = 0;
-    uint8_t p1 = 0;
-    if (rest & 8u) p8 = *(const REMP_GLOBAL Part8*)(src + off);
-    if (rest & 4u) p4 = *(const REMP_GLOBAL Part4*)(src + at4);
-    if (rest & 2u) p2 = *(const REMP_GLOBAL Part2*)(src + at2);
-    if (rest & 1u) p1 = *(const REMP_GLOBAL uint8_t*)(src + at1);
-    if (rest & 8u) *(REMP_GLOBAL Part8*)(dst + off) = p8;
-    if (rest & 4u) *(REMP_GLOBAL Part4*)(dst + at4) = p4;
-    if (rest & 2u) *(REMP_GLOBAL Part2*)(dst + at2) = p2;
-    if (rest & 1u) *(REMP_GLOBAL uint8_t*)(dst + at1) = p1;
+    Vec16Any w;
+    uint64_t p8;
+    uint32_t p4;
+    uint16_t p2;
+    uint8_t p1;
+
+    __device__ __forceinline__ void load(uint64_t src, uint32_t left) {
+        if (left >= kVecBytes) {
+            w = __builtin_nontemporal_load((const REMP_GLOBAL Vec16Any*)src);
+            return;
+        }
+        const uint32_t at4 = left & 8u, at2 = at4 + (left & 4u), at1 = at2 + (left & 2u);
+        if (left & 8u) p8 = *(const REMP_GLOBAL Part8*)src;
+        if (left & 4u) p4 = *(const REMP_GLOBAL Part4*)(src + at4);
+        if (left & 2u) p2 = *(const REMP_GLOBAL Part2*)(src + at2);
+        if (left & 1u) p1 = *(const REMP_GLOBAL uint8_t*)(src + at1);
+    }
+    __device__ __forceinline__ void store(uint64_t dst, uint32_t left) const {
+        if (left >= kVecBytes) {
+            __builtin_nontemporal_store(w, (REMP_GLOBAL Vec16Any*)dst);
+            return;
+        }
+        const uint32_t at4 = left & 8u, at2 = at4 + (left & 4u), at1 = at2 + (left & 2u);
+        if (left & 8u) *(REMP_GLOBAL Part8*)dst = p8;
+        if (left & 4u) *(REMP_GLOBAL Part4*)(dst + at4) = p4;
+        if (left & 2u) *(REMP_GLOBAL Part2*)(dst + at2) = p2;
+        if (left & 1u) *(REMP_GLOBAL uint8_t*)(dst + at1) = p1;
+    }
+};
+
+// Bytes [off, off + 16) of a run of `len` bytes, or what the run still has of them.
+template <bool ODD>
+__device__ __forceinline__ void move_vector(uint64_t src, uint64_t dst, uint32_t off, uint32_t len) {
+    Moved<ODD ? 0 : 16> m;
+    m.load(src + off, len - off);
+    m.store(dst + off, len - off);
 }
 
 template <int ITEMS>

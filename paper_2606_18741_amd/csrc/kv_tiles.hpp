@@ -67,7 +67,6 @@ struct TileArgs {
 static_assert(sizeof(TileArgs) < 4096, "tile kernel arguments must stay below 4 KiB");
 
 __device__ __forceinline__ BlockDesc load_desc_scalar(const BlockDesc* desc, uint32_t i) {
-    typedef int Int4 __attribute__((ext_vector_type(4)));
     const Int4 v = ((const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(desc)))[i];
     return BlockDesc{v.x, v.y, v.z, v.w};
 }
@@ -804,7 +803,6 @@ static_assert(sizeof(LocalStripArgs) < 4096, "local strip kernel arguments must 
 
 template <bool TO_ROCM, int EB>
 __global__ __launch_bounds__(kMaxStripThreads) void copy_local_strips(const LocalStripArgs a) {
-    typedef int Int4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr uint32_t M = kVecBytes / EB;
     if (stale_descriptors(a.check)) return;
@@ -812,20 +810,21 @@ __global__ __launch_bounds__(kMaxStripThreads) void copy_local_strips(const Loca
     const uint32_t kv = blockIdx.z, bs = a.old_block_size, v = threadIdx.x, u = xcd_position(blockIdx.x);
     const uint32_t i = fast_div(u, it.strips_magic, it.strips_shift), s = u - i * it.strips;
     if (i >= a.n_new_desc) return;
-    const LocalUnit b = load_local_unit<true>(
+    const LocalUnit<1> b = load_local_unit<1>(
         a, (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(a.new_desc)),
         (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(a.old_desc)),
         (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(a.tok_off)),
-        (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(a.old_blk_off)), i);
-    if (b.n < b.d.n && v == 0) *a.flag = kFlagTables;
-    const uint32_t n = static_cast<uint32_t>(min(b.n, b.d.n));
+        (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(a.old_blk_off)), i, 0);
+    const int32_t on = b.t0 >= 0 && b.q * bs == static_cast<uint32_t>(b.t0) ? b.o.v.n : 0;
+    if (on < b.n && v == 0) *a.flag = kFlagTables;
+    const uint32_t n = static_cast<uint32_t>(min(on, b.n));
     const bool tail = s == it.strips - 1;
     const uint32_t cols = tail ? it.last : a.strip, c0 = s * a.strip;
     const uint32_t lrow = (a.strip + 1) * kVecBytes;
     const uint64_t src = (kv ? it.src_v : it.src_k) +
-                         static_cast<uint64_t>(static_cast<uint32_t>(b.block)) * static_cast<uint64_t>(a.old_block_stride);
+                         static_cast<uint64_t>(static_cast<uint32_t>(b.o.v.block)) * static_cast<uint64_t>(a.old_block_stride);
     const uint64_t dst = (kv ? it.dst_v : it.dst_k) +
-                         static_cast<uint64_t>(static_cast<uint32_t>(b.d.block)) * static_cast<uint64_t>(a.new_block_stride);
+                         static_cast<uint64_t>(static_cast<uint32_t>(b.block)) * static_cast<uint64_t>(a.new_block_stride);
     // in the other pool: column c0 + col of row `row`
     const uint32_t row = fast_div(v, tail ? it.last_magic : a.strip_magic, tail ? it.last_shift : a.strip_shift);
     const uint32_t col = v - row * cols, j = fast_div(c0 + col, a.head_magic, a.head_shift);

@@ -181,9 +181,14 @@ static uint32_t shares_lines(uint64_t row, uint64_t stride, bool odd) {
 // Units of `vpu` vectors that one launch can number: a dispatch counts its work-items in 32 bits, and `shares`
 // lanes of the grid take each vector number.
 static uint32_t units_per_launch(int64_t n_desc, uint64_t vpu, uint32_t shares) {
-    const uint64_t most = ((uint64_t(1) << 32) - kMaxRunThreads * uint64_t(8 * kXcdRun)) / (vpu * shares);
+    const uint64_t most = ((uint64_t(1) << 32) - 4 * kMaxRunThreads * uint64_t(8 * kXcdRun)) / (vpu * shares);
     return static_cast<uint32_t>(std::min<uint64_t>(static_cast<uint64_t>(n_desc), most));
 }
+
+// Bytes of the words that rows of at most `row` bytes go by when they are not whole vectors, all aligned: 8, or 0, which is
+// 16 at any address.  Words leave no odd part at a row's end, which is an instruction of its own; longer rows have few
+// of those, and 4-byte words take too many instructions (rates at the callers).
+static int odd_words(uint64_t bits, uint32_t row, uint32_t most) { return bits % 8 == 0 && row <= most ? 8 : 0; }
 
 // Slices per launch of copy_runs: kMaxItems, or as many as bring a launch to kLaunchBytes where slices are small, in
 // equal launches.
@@ -814,22 +819,16 @@ struct HostLocal {
     uint32_t row_bytes;
 };
 
-template <int N, bool SAME>
-static void launch_local_s(const LocalArgs& a, dim3 grid, int threads, int vec, hipStream_t stream) {
+template <int N, int M>
+static void launch_local_n(const LocalArgs& a, dim3 grid, int threads, int vec, int words, hipStream_t stream) {
     if (vec == 16)
-        hipLaunchKernelGGL((copy_local<N, SAME, 16>), grid, dim3(threads), 0, stream, a);
+        hipLaunchKernelGGL((copy_local<N, M, 16, 1>), grid, dim3(threads), 0, stream, a);
+    else if (vec == 8 && words == 2)
+        hipLaunchKernelGGL((copy_local<N, M, 8, 2>), grid, dim3(threads), 0, stream, a);
     else if (vec == 8)
-        hipLaunchKernelGGL((copy_local<N, SAME, 8>), grid, dim3(threads), 0, stream, a);
-    else if (vec == 4)
-        hipLaunchKernelGGL((copy_local<N, SAME, 4>), grid, dim3(threads), 0, stream, a);
+        hipLaunchKernelGGL((copy_local<N, M, 8, kLocalWords>), grid, dim3(threads), 0, stream, a);
     else
-        hipLaunchKernelGGL((copy_local<N, SAME, 0>), grid, dim3(threads), 0, stream, a);
-}
-
-template <int N>
-static void launch_local_n(const LocalArgs& a, dim3 grid, int threads, bool same, int vec, hipStream_t stream) {
-    if (same) launch_local_s<N, true>(a, grid, threads, vec, stream);
-    else launch_local_s<N, false>(a, grid, threads, vec, stream);
+        hipLaunchKernelGGL((copy_local<N, M, 0, 1>), grid, dim3(threads), 0, stream, a);
 }
 
 template <bool TO_ROCM>
@@ -1022,18 +1021,15 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
         bits |= it.src_k | it.src_v | it.dst_k | it.dst_v | it.row_bytes;
         max_row = std::max(max_row, it.row_bytes);
     }
-    // Rows that are whole 8-byte words, all aligned, go by words, and short ones by 4-byte words:
-    // 16-byte vectors at any address leave a part of every row to smaller ones (MI355X, us so /
-    // with those: rows of 200 bytes 547 / 866, of 100 497 / 657, but of 300 by 4-byte words 1750 / 1006).
-    // Not where the block sizes differ: each lane then finds its row's source by itself (rows of 200 bytes, blocks of 64
-    // and 20: 1163 us by words, 1147 so).
+    // Rows that are not whole vectors (MI355X, us; before: rows resolved into LDS, aligned words): 200 of 400 bytes in
+    // blocks of 20, before 719, 8-byte words (4 to a lane) 690, any 779; in blocks of 64 706 / 666 / 757; blocks of 64 to
+    // 20 718 / 704 / 776; 520 of 1040 bytes 857 / 756 / 746; any for rows of 4-byte words, 100 of 200 bytes 1268 / 1095.
     const bool odd = bits % kVecBytes != 0;
-    const int vec = !odd ? 16 : bo != bn ? 0 : bits % 8 == 0 ? 8 : bits % 4 == 0 && max_row <= 128 ? 4 : 0;
-    const uint32_t lane_bytes = vec ? vec : kVecBytes;
-    const auto vectors = [&](uint32_t row) {
-        return static_cast<uint64_t>(bn) * ((row + lane_bytes - 1) / lane_bytes);
-    };
+    const int vec = odd ? odd_words(bits, max_row, kLocalWordRow) : 16;
+    const uint32_t word = vec ? vec : kVecBytes;   // bytes of a word
+    const auto vectors = [&](uint32_t row) { return static_cast<uint64_t>(bn) * ((row + word - 1) / word); };
     const uint64_t max_vpu = vectors(max_row);
+    const uint32_t words = vec != 8 ? 1 : max_vpu >= 64 * kLocalWords ? kLocalWords : 2;   // words of a lane
     if (bn > kMaxLocalRows) return fail(REMP_E_UNSUPPORTED, "new block size above the local-copy row limit");
     if (max_vpu >= kMaxUnitVectors) return fail(REMP_E_UNSUPPORTED, "a block of one slice exceeds 2^31 vectors");
     const int threads = run_threads(p, kRunThreads);
@@ -1063,7 +1059,8 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
     }
     for (size_t first = 0; first < items.size(); first += kMaxLocalItems) {
         const size_t cnt = std::min<size_t>(kMaxLocalItems, items.size() - first);
-        int n = 1;   // units that a wave can meet, as in launch_copy
+        int n = 1;        // units that a wave can meet, as in launch_copy
+        uint32_t m = 1;   // old blocks that the rows of one of them can come from
         for (size_t i = 0; i < cnt; ++i) {
             const HostLocal& h = items[first + i];
             LocalItem& c = a.items[i];
@@ -1073,26 +1070,40 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
             c.dst_v = h.dst_v;
             c.row_bytes = h.row_bytes;
             c.vpu = static_cast<uint32_t>(vectors(h.row_bytes));
-            const FastDiv fv = make_fastdiv((h.row_bytes + lane_bytes - 1) / lane_bytes);
+            const uint32_t vpr = (h.row_bytes + word - 1) / word;
+            const FastDiv fv = make_fastdiv(vpr);
             const FastDiv fu = make_fastdiv(c.vpu);
             c.vpr_magic = fv.magic;
             c.vpr_shift = static_cast<uint16_t>(fv.shift);
             c.vpu_magic = fu.magic;
             c.vpu_shift = static_cast<uint16_t>(fu.shift);
-            const int m = units_per_wave(c.vpu);
-            n = n == 0 || m == 0 ? 0 : std::max(n, m);
+            const int u = units_per_wave(c.vpu, 64 * words);
+            n = n == 0 || u == 0 ? 0 : std::max(n, u);
+            const uint32_t rows = std::min<uint32_t>(bn, pieces_per_wave(vpr, 64 * words));
+            if (bo != bn) m = std::max(m, (rows + bo - 2) / bo + 1);
         }
+        // By scalar loads: one or two old blocks of each of one or two new ones, or one of each of four of equal size.
         for (int64_t d0 = 0; d0 < n_desc; d0 += per_launch) {
             a.new_desc = desc + d0;
             a.n_new_desc = static_cast<uint32_t>(std::min<int64_t>(per_launch, n_desc - d0));
-            const uint64_t wgs = (a.n_new_desc * max_vpu + threads - 1) / threads;
+            const uint64_t wgs = (a.n_new_desc * max_vpu + threads * words - 1) / (threads * words);
             const dim3 grid(static_cast<uint32_t>(a.xcd ? xcd_grid(wgs) : wgs), static_cast<uint32_t>(cnt), 2);
             switch (n) {
-                case 1: launch_local_n<1>(a, grid, threads, bo == bn, vec, stream); break;
-                case 2: launch_local_n<2>(a, grid, threads, bo == bn, vec, stream); break;
-                case 4: launch_local_n<4>(a, grid, threads, bo == bn, vec, stream); break;
-                case 8: launch_local_n<8>(a, grid, threads, bo == bn, vec, stream); break;
-                default: launch_local_n<0>(a, grid, threads, bo == bn, vec, stream); break;
+                case 1:
+                    if (m == 1) launch_local_n<1, 1>(a, grid, threads, vec, words, stream);
+                    else if (m == 2) launch_local_n<1, 2>(a, grid, threads, vec, words, stream);
+                    else launch_local_n<1, 0>(a, grid, threads, vec, words, stream);
+                    break;
+                case 2:
+                    if (m == 1) launch_local_n<2, 1>(a, grid, threads, vec, words, stream);
+                    else if (m == 2) launch_local_n<2, 2>(a, grid, threads, vec, words, stream);
+                    else launch_local_n<2, 0>(a, grid, threads, vec, words, stream);
+                    break;
+                case 4:
+                    if (bo == bn) launch_local_n<4, 1>(a, grid, threads, vec, words, stream);
+                    else launch_local_n<4, 0>(a, grid, threads, vec, words, stream);
+                    break;
+                default: launch_local_n<0, 1>(a, grid, threads, vec, words, stream); break;
             }
             if (remp_status st = hip_check(hipGetLastError(), "copy_local launch")) return st;
         }
