@@ -16,40 +16,76 @@ namespace remp {
 
 
 // One launch copies the same part of several slices (grid y) for K and V (grid z); grid x numbers the
-// vectors of a slice's live blocks, block after block, and a wave takes 64 of them: 1 KiB, one load and
-// one store per lane.  Bound by HBM.  The waves are as short as they can be: with one vector in
+// words of a slice's live blocks, block after block, and a wave takes 1 KiB of them.  Bound by HBM.
+// Of aligned 16-byte words the waves are as short as they can be: with one vector in
 // flight per lane the chip already has 8 MiB in flight at full occupancy, and more loads per lane or
 // longer workgroups only spread the accesses over more DRAM rows at a time (kRunThreads has the rates).
 // Nothing passes through LDS and no wave waits for another.  K and V are separate runs of the grid, not
 // alternating units: +1.2% on 4 KiB units, +3.2% on 32 KiB units.
 // Measured on MI355X against the kernel before it (128 threads x 4 vectors per 8 KiB, descriptors through
 // LDS, flat loads): random 4 KiB blocks packed 5.99 -> 6.29 TB/s, 32 KiB blocks 5.90 -> 6.40 TB/s.
-//   CONTIG  the slice takes whole paged rows, so a block's live rows are one run of bytes on both sides
-//   ODD     rows are not whole vectors, or some address is not 16-byte aligned
-template <bool PACK, int N, bool CONTIG, bool ODD, int ITEMS>
+// Rows that are not whole vectors, or not aligned, go by words of V = 8 bytes, K to a lane, or (V = 0) by 16 bytes at any
+// address and smaller parts at the end of a row (run_words has the rates).
+// What a wave's words are:
+//   kRuns     of whole paged rows, so a block's live rows are one run of bytes on both sides
+//   kCutRows  of parts of rows, row after row, cut wherever the wave's words end
+//   kRows     the same, but of the whole rows that fit into the wave, K and V by turns
+enum RunShape { kRuns, kCutRows, kRows };
+
+template <bool PACK, int N, RunShape SHAPE, int V, int K, int ITEMS>
 __global__ __launch_bounds__(kMaxRunThreads) void copy_runs(const CopyArgs<ITEMS> args) {
+    constexpr uint32_t W = V ? V : kVecBytes;   // bytes of a word
     if (stale_descriptors(args.check)) return;
     const CopyItem& it = args.items[blockIdx.y];
-    const uint32_t kv = blockIdx.z;
-    BlockDesc d;
-    uint32_t r;
-    if (!pick_unit<N>(args.desc, args.n_desc, wave_first(args.xcd), threadIdx.x & 63u, it.vpu, it.vpu_magic, it.vpu_shift, &d,
-                      &r))
-        return;
-    const uint32_t row_bytes = it.row_bytes, n = static_cast<uint32_t>(d.n);
-    uint64_t paged = (kv ? it.paged_v : it.paged_k) + static_cast<uint64_t>(static_cast<uint32_t>(d.block)) *
-                                                          static_cast<uint64_t>(args.block_stride);
-    uint64_t stage = it.stage + (static_cast<uint64_t>(kv) * args.total_tokens + static_cast<uint32_t>(d.tok)) * row_bytes;
-    uint32_t off = r * kVecBytes, len = n * row_bytes;
-    if (!CONTIG) {
-        const uint32_t vpr = (row_bytes + kVecBytes - 1) / kVecBytes;
-        const uint32_t row = fast_div(r, it.vpr_magic, it.vpr_shift);
-        paged += static_cast<uint64_t>(row) * args.row_stride;
-        stage += static_cast<uint64_t>(row) * row_bytes;
-        off = (r - row * vpr) * kVecBytes;
-        len = row < n ? row_bytes : 0;
+    const uint32_t row_bytes = it.row_bytes, lane = threadIdx.x & 63u;
+    const uint32_t vpr = (row_bytes + W - 1) / W;
+    WaveUnits<N> units;
+    uint32_t kv = blockIdx.z, first;
+    if (SHAPE == kRows) {
+        kv = blockIdx.x & 1u;
+        first = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(
+                    static_cast<int>(((blockIdx.x >> 1) * blockDim.x + threadIdx.x) / 64))) * it.rows;
+    } else {
+        first = wave_first(args.xcd) * K;
     }
-    if (off < len) move_vector<ODD>(PACK ? paged : stage, PACK ? stage : paged, off, len);
+    if (!units.load(args.desc, args.n_desc, first, it.vpu, it.vpu_magic, it.vpu_shift)) return;
+    Moved<V> word[K];
+    uint64_t dst[K];
+    uint32_t left[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        left[k] = 0;
+        BlockDesc d;
+        uint32_t r, i = k * 64 + lane, c = 0;
+        if (SHAPE == kRows) {
+            const uint32_t j = fast_div(i, it.vpr_magic, it.vpr_shift);
+            if (j >= it.rows) continue;
+            c = i - j * vpr;
+            i = j;
+        }
+        if (!units.pick(args.desc, args.n_desc, i, it.vpu, it.vpu_magic, it.vpu_shift, &d, &r)) continue;
+        const uint32_t n = static_cast<uint32_t>(d.n);
+        uint64_t paged = (kv ? it.paged_v : it.paged_k) + static_cast<uint64_t>(static_cast<uint32_t>(d.block)) *
+                                                              static_cast<uint64_t>(args.block_stride);
+        uint64_t stage =
+            it.stage + (static_cast<uint64_t>(kv) * args.total_tokens + static_cast<uint32_t>(d.tok)) * row_bytes;
+        uint32_t off = r * W, len = n * row_bytes;
+        if (SHAPE != kRuns) {
+            const uint32_t row = SHAPE == kRows ? r : fast_div(r, it.vpr_magic, it.vpr_shift);
+            if (SHAPE == kCutRows) c = r - row * vpr;
+            paged += static_cast<uint64_t>(row) * args.row_stride;
+            stage += static_cast<uint64_t>(row) * row_bytes;
+            off = c * W;
+            len = row < n ? row_bytes : 0;
+        }
+        if (off >= len) continue;
+        left[k] = len - off;
+        dst[k] = (PACK ? stage : paged) + off;
+        word[k].load((PACK ? paged : stage) + off, left[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (left[k]) word[k].store(dst[k], left[k]);
 }
 
 
@@ -187,7 +223,7 @@ __device__ __forceinline__ bool find_source(const Args& a, const LocalUnit<M>& x
 
 template <int N, int M, int V, int K>
 __global__ __launch_bounds__(kMaxRunThreads) void copy_local(const LocalArgs args) {
-    constexpr uint32_t W = V ? V : kVecBytes;   // bytes of a word
+    constexpr uint32_t W = V ? V : kVecBytes;   // as in copy_runs
     if (stale_descriptors(args.check)) return;
     const LocalItem& it = args.items[blockIdx.y];
     const uint32_t kv = blockIdx.z, w0 = wave_first(args.xcd) * K, lane = threadIdx.x & 63u, vpu = it.vpu;

@@ -90,7 +90,7 @@ constexpr int kRowsPackThreads = 256;
 constexpr int kMaxRunThreads = 1024;   // the most the tuning override asks for
 constexpr int kScanThreads = 1024;
 // Rows that are not whole vectors go by 8-byte words up to these bytes, where they are aligned to that.
-constexpr uint32_t kLocalWordRow = 512;
+constexpr uint32_t kPackWordRow = 512, kUnpackWordRow = 256, kLocalWordRow = 512;
 // Such words of a lane: 2 (1 KiB to a wave), and 4 in the local copy where a block has as many, so that its look-ups serve
 // more bytes (MI355X, us, 2 / 4 words: 200-byte rows in blocks of 64 718 / 666, blocks of 64 to 20 706 / 672; but of 72
 // bytes, blocks of 32 to 16, 897 / 1100).
@@ -101,11 +101,12 @@ struct CopyItem {
     uint64_t paged_v;
     uint64_t stage;       // first byte of the slice in its staging buffer (K part)
     uint32_t row_bytes;   // head_count * head_dim * elem_bytes
-    uint32_t vpr_magic;   // fast division by vectors per row
-    uint32_t vpu;         // vectors per (block, K or V) unit
+    uint32_t vpr_magic;   // fast division by words per row
+    uint32_t vpu;         // words (kRows: rows) per (block, K or V) unit
     uint32_t vpu_magic;   // fast division by vpu
     uint16_t vpr_shift;
     uint16_t vpu_shift;
+    uint32_t rows;        // rows per wave (kRows)
 };
 
 // The unit (live block, K or V) that a lane works on.  The words of a slice's units (16-byte vectors, or words of 8 or 4

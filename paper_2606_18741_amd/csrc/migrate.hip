@@ -200,26 +200,30 @@ static size_t items_per_launch(size_t slices, uint64_t slice_bytes, bool odd) {
 }
 
 template <bool PACK, int N>
-static void launch_runs_n(const CopyArgs<kMaxSmallItems>& big, dim3 grid, int threads, bool contig, bool odd,
+static void launch_runs_n(const CopyArgs<kMaxSmallItems>& big, dim3 grid, int threads, RunShape shape, int vec,
                           hipStream_t stream) {
-    if (grid.y > kMaxItems) {   // never odd (items_per_launch)
-        if (contig)
-            hipLaunchKernelGGL((copy_runs<PACK, N, true, false, kMaxSmallItems>), grid, dim3(threads), 0, stream, big);
+    if (grid.y > kMaxItems) {   // always of whole vectors (items_per_launch)
+        if (shape == kRuns)
+            hipLaunchKernelGGL((copy_runs<PACK, N, kRuns, 16, 1, kMaxSmallItems>), grid, dim3(threads), 0, stream, big);
         else
-            hipLaunchKernelGGL((copy_runs<PACK, N, false, false, kMaxSmallItems>), grid, dim3(threads), 0, stream, big);
+            hipLaunchKernelGGL((copy_runs<PACK, N, kCutRows, 16, 1, kMaxSmallItems>), grid, dim3(threads), 0, stream, big);
         return;
     }
     CopyArgs<kMaxItems> a;
     static_assert(offsetof(CopyArgs<kMaxItems>, items) == offsetof(CopyArgs<kMaxSmallItems>, items), "same head");
     std::memcpy(&a, &big, sizeof(a));
-    if (contig && !odd)
-        hipLaunchKernelGGL((copy_runs<PACK, N, true, false, kMaxItems>), grid, dim3(threads), 0, stream, a);
-    else if (contig)
-        hipLaunchKernelGGL((copy_runs<PACK, N, true, true, kMaxItems>), grid, dim3(threads), 0, stream, a);
-    else if (!odd)
-        hipLaunchKernelGGL((copy_runs<PACK, N, false, false, kMaxItems>), grid, dim3(threads), 0, stream, a);
+    if (shape == kRuns && vec == 16)
+        hipLaunchKernelGGL((copy_runs<PACK, N, kRuns, 16, 1, kMaxItems>), grid, dim3(threads), 0, stream, a);
+    else if (shape == kRuns)
+        hipLaunchKernelGGL((copy_runs<PACK, N, kRuns, 0, 1, kMaxItems>), grid, dim3(threads), 0, stream, a);
+    else if (vec == 16)
+        hipLaunchKernelGGL((copy_runs<PACK, N, kCutRows, 16, 1, kMaxItems>), grid, dim3(threads), 0, stream, a);
+    else if (vec == 8)
+        hipLaunchKernelGGL((copy_runs<PACK, N, PACK ? kCutRows : kRows, 8, 2, kMaxItems>), grid, dim3(threads), 0, stream, a);
+    else if (PACK || shape == kCutRows)
+        hipLaunchKernelGGL((copy_runs<PACK, N, kCutRows, 0, 1, kMaxItems>), grid, dim3(threads), 0, stream, a);
     else
-        hipLaunchKernelGGL((copy_runs<PACK, N, false, true, kMaxItems>), grid, dim3(threads), 0, stream, a);
+        hipLaunchKernelGGL((copy_runs<PACK, N, PACK ? kCutRows : kRows, 0, 1, kMaxItems>), grid, dim3(threads), 0, stream, a);
 }
 
 template <bool PACK>
@@ -240,9 +244,21 @@ static remp_status launch_copy(const remp_kv_plan_t& p, const std::vector<HostSl
     const bool odd = bits % kVecBytes != 0;
     // a contiguous block is indexed by its bytes in 32 bits
     contig &= static_cast<uint64_t>(bs) * max_row < (uint64_t(1) << 31);
+    // Parts of rows that are not whole vectors.  Unpacked, their ends are parts of lines that no other wave should
+    // write: whole rows to a wave.  MI355X, blocks of 16, half of each row (us; before: LDS descriptors, aligned words):
+    //   pack    72 B before 997, 8-byte words 985, any 1047    136 B 1062 / 948 / 990     520 B 768 / 726 / 707
+    //           36 B before 1275, any 1121                     100 B 1325 / 1039          260 B 1198 / 834
+    //   unpack  72 B before 1685, whole rows by 8-byte words 1599, any 1894, cut rows by words 1675
+    //           136 B 1609 / 1679 / 1737 / 1768    200 B 1402 / 1381 / 1385 / 1447    328 B 1087 / 1106 / 1055 / 1180
+    //           36 B before 2052, whole rows any 1744, cut any 1776    100 B 1890 / 1949 / 1956    260 B 1453 / 1234 / 1331
+    //           520 B before 941, cut any 935, whole rows 938
+    const int vec = !odd ? 16 : contig ? 0 : odd_words(bits, max_row, PACK ? kPackWordRow : kUnpackWordRow);
+    const uint32_t word = vec ? vec : kVecBytes, words = kVecBytes / word;   // bytes of a word; words of a lane
+    const uint32_t max_vpr = (max_row + word - 1) / word;
+    const RunShape shape = contig ? kRuns : !PACK && odd && 2 * max_vpr <= 64 * words ? kRows : kCutRows;
     const auto vectors = [&](uint32_t row) {
         return contig ? (static_cast<uint64_t>(bs) * row + kVecBytes - 1) / kVecBytes
-                      : static_cast<uint64_t>(bs) * ((row + kVecBytes - 1) / kVecBytes);
+                      : static_cast<uint64_t>(bs) * ((row + word - 1) / word);
     };
     const uint64_t max_vpu = vectors(max_row);
     if (max_vpu >= kMaxUnitVectors) return fail(REMP_E_UNSUPPORTED, "a block of one slice exceeds 2^31 vectors");
@@ -257,7 +273,6 @@ static remp_status launch_copy(const remp_kv_plan_t& p, const std::vector<HostSl
     for (const HostSlice& s : slices) a.xcd |= shares_lines(s.row_bytes, a.row_stride, odd);
     const BlockDesc* desc = reinterpret_cast<const BlockDesc*>(ws + desc_off);
     const uint32_t per_launch = units_per_launch(n_desc, max_vpu, 1);
-
     if (g_trace_start) {
         if (remp_status st = hip_check(hipEventRecord(g_trace_start, stream), "trace start event")) return st;
     }
@@ -273,26 +288,38 @@ static remp_status launch_copy(const remp_kv_plan_t& p, const std::vector<HostSl
             c.stage = s.stage;
             c.row_bytes = s.row_bytes;
             c.vpu = static_cast<uint32_t>(vectors(s.row_bytes));
-            const FastDiv fv = make_fastdiv((s.row_bytes + kVecBytes - 1) / kVecBytes);
+            int m = units_per_wave(c.vpu, 64 * words);
+            if (shape == kRows) {   // numbered in rows instead of words
+                c.rows = 64 * words / ((s.row_bytes + word - 1) / word);
+                c.vpu = static_cast<uint32_t>(bs);
+                m = units_per_wave(c.vpu, c.rows);
+            }
+            const FastDiv fv = make_fastdiv((s.row_bytes + word - 1) / word);
             const FastDiv fu = make_fastdiv(c.vpu);
             c.vpr_magic = fv.magic;
             c.vpr_shift = static_cast<uint16_t>(fv.shift);
             c.vpu_magic = fu.magic;
             c.vpu_shift = static_cast<uint16_t>(fu.shift);
-            const int m = units_per_wave(c.vpu);
             n = n == 0 || m == 0 ? 0 : std::max(n, m);
         }
         for (int64_t d0 = 0; d0 < n_desc; d0 += per_launch) {
             a.desc = desc + d0;
             a.n_desc = static_cast<uint32_t>(std::min<int64_t>(per_launch, n_desc - d0));
-            const uint64_t wgs = (a.n_desc * max_vpu + threads - 1) / threads;
-            const dim3 grid(static_cast<uint32_t>(a.xcd ? xcd_grid(wgs) : wgs), static_cast<uint32_t>(cnt), 2);
+            dim3 grid(0, static_cast<uint32_t>(cnt), 2);
+            if (shape == kRows) {
+                const uint64_t rows = static_cast<uint64_t>(64 * words / max_vpr) * (threads / 64);   // of a workgroup
+                grid.x = static_cast<uint32_t>(2 * ((a.n_desc * static_cast<uint64_t>(bs) + rows - 1) / rows));
+                grid.z = 1;
+            } else {
+                const uint64_t wgs = (a.n_desc * max_vpu + threads * words - 1) / (threads * words);
+                grid.x = static_cast<uint32_t>(a.xcd ? xcd_grid(wgs) : wgs);
+            }
             switch (n) {
-                case 1: launch_runs_n<PACK, 1>(a, grid, threads, contig, odd, stream); break;
-                case 2: launch_runs_n<PACK, 2>(a, grid, threads, contig, odd, stream); break;
-                case 4: launch_runs_n<PACK, 4>(a, grid, threads, contig, odd, stream); break;
-                case 8: launch_runs_n<PACK, 8>(a, grid, threads, contig, odd, stream); break;
-                default: launch_runs_n<PACK, 0>(a, grid, threads, contig, odd, stream); break;
+                case 1: launch_runs_n<PACK, 1>(a, grid, threads, shape, vec, stream); break;
+                case 2: launch_runs_n<PACK, 2>(a, grid, threads, shape, vec, stream); break;
+                case 4: launch_runs_n<PACK, 4>(a, grid, threads, shape, vec, stream); break;
+                case 8: launch_runs_n<PACK, 8>(a, grid, threads, shape, vec, stream); break;
+                default: launch_runs_n<PACK, 0>(a, grid, threads, shape, vec, stream); break;
             }
             if (remp_status st = hip_check(hipGetLastError(), PACK ? "pack launch" : "unpack launch")) return st;
         }
