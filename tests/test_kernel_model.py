@@ -10,6 +10,7 @@ local copy without its negative-token check) must be caught.
 """
 from __future__ import annotations
 
+import dataclasses
 import os
 
 import numpy as np
@@ -35,6 +36,13 @@ def check_model(w, inp=None, windows=None, local=False, lo=km.NHD, ln=km.NHD, wg
     m = km.Migration(w, inp, lo, ln, data=True, wg_bytes=wg_bytes, seed=seed)
     flags = m.migrate(windows, local)
     assert all(f == 0 for f in flags), flags
+    for r in m.old_host:
+        _coverage(m.pack_launches(r, 0, m.L, local), m.n_old)
+    for q in m.new_host:
+        _coverage(m.unpack_launches(q, 0, m.L, local), m.n_new)
+    if local:
+        for r in set(m.old_host) & set(m.new_host):
+            _coverage(m.local_launches(r, 0, m.L), m.n_new)
     pairs = _staged_pairs(m, local)
     ref_new = {q: {l: a.copy() for l, a in per.items()} for q, per in m.new_host.items()}
     st = oracle.reshard(m.old_host, ref_new, T(*w.old_topo), T(*w.new_topo), w.num_layers, w.num_kv_heads,
@@ -188,16 +196,39 @@ def test_model_fuzz_layouts(seed, lo, ln):
 # full-size launch shapes: grid order, chunk coverage, sampled workgroups in bounds
 # ---------------------------------------------------------------------------
 
-def _coverage(launch: km.Launch, n_desc: int) -> None:
-    """The cell order is a bijection of the grid, and the workgroups of each slice cover its 2 * n_desc
-    (block, K/V) units exactly once."""
-    gx, gy = launch.grid
-    cx, cy = km.grid_cells(gx, gy, launch.xcd)
-    assert np.unique(cy * gx + cx).size == gx * gy
-    C = launch.args["C"]
-    units = 2 * n_desc
-    assert (gx - 1) * C < units <= gx * C
-    assert C <= km.MAX_UNITS_PER_WG
+def _coverage(launches, n_desc: int) -> None:
+    """The waves of the launches take every word (row, strip, tile) of every slice's n_desc live blocks once, K and V: by
+    the kernels' own numbering no two of a launch take the same, what they take runs on without a gap from the first
+    to the last, and launches that share a slice's blocks adjoin."""
+    blocks = {}
+    for Lc in launches:
+        a = Lc.args
+        part, first, count, size = km.wave_spans(Lc)
+        order = np.lexsort((first, part))
+        part, first, count, size = part[order], first[order], count[order], size[order]
+        new = np.concatenate([[True], part[1:] != part[:-1]])
+        assert (first[new] == 0).all(), "a part does not begin with its first word"
+        assert (first[1:] == (first + count)[:-1])[~new[1:]].all(), "two waves overlap, or leave words between them"
+        last = np.concatenate([new[1:], [True]])
+        assert ((first + count)[last] >= size[last]).all(), "the grid ends before the last word"
+        held = np.bincount(part, weights=np.clip(size - first, 0, count))[part[last]]
+        assert (held == size[last]).all()
+        parts = 2 * len(a["items"]) if "items" in a else 2 * len(a["groups"])
+        if Lc.kernel in ("copy_tile_groups", "copy_local_tiles"):
+            parts //= 2                                      # their tiles are K's and V's
+        elif Lc.kernel in ("copy_rows", "copy_pieces"):
+            parts *= a["nseg"] if a["order"] == "share" or (Lc.kernel == "copy_pieces" and a["pack"]) else 1
+        assert last.sum() == parts, "a slice's K or V is left out"
+        keys = [s.stage if hasattr(s, "stage") else s.dst_k for s in a["items"]] if "items" in a else \
+            [g[0].stage for g in a["groups"]]
+        for key in keys:
+            blocks.setdefault(key, []).append((a.get("d0", 0), a.get("n_desc", a.get("n_new"))))
+    for spans in blocks.values():
+        at = 0
+        for d0, n in sorted(spans):
+            assert d0 == at and n > 0, "launches of one slice do not adjoin"
+            at += n
+        assert at == n_desc, "blocks are left out"
 
 
 @pytest.mark.parametrize("name", REDUCED)
@@ -208,19 +239,31 @@ def test_model_full_size_launch_shapes(name):
     ro, qn = w.role
     launches = m.pack_launches(ro, 0, w.num_layers)
     assert launches
-    for Lc in launches:
-        if Lc.kernel in ("copy_slices", "copy_rows"):
-            _coverage(Lc, m.n_old)
+    _coverage(launches, m.n_old)
     assert m.pack(ro, sample=48) == 0
-    launches = m.unpack_launches(qn, 0, w.num_layers)
-    for Lc in launches:
-        if Lc.kernel in ("copy_slices", "copy_rows"):
-            _coverage(Lc, m.n_new)
+    _coverage(m.unpack_launches(qn, 0, w.num_layers), m.n_new)
     assert m.unpack(qn, sample=48) == 0
     if (ro, qn) in m.pairs and ro == qn:
-        for Lc in m.local_launches(ro, 0, w.num_layers):
-            _coverage(Lc, m.n_new)
+        _coverage(m.local_launches(ro, 0, w.num_layers), m.n_new)
         assert m.copy_local(ro, sample=48) == 0
+
+
+def test_coverage_check_sees_what_is_missing():
+    """A grid one workgroup short, workgroups numbered twice, a launch left out: each fails the coverage check."""
+    w = synthkv.GQA_70B
+    m = km.Migration(w, synthkv.make_inputs(w), data=False)
+    launches = m.pack_launches(0, 0, 8)
+    _coverage(launches, m.n_old)
+    (one,) = launches
+    for planted in (dataclasses.replace(one, grid=(one.grid[0] - 1, one.grid[1])),
+                    dataclasses.replace(one, grid=(one.grid[0], one.grid[1] - 1)),
+                    dataclasses.replace(one, xcd=True),            # of a grid that is no multiple of the XCD runs
+                    dataclasses.replace(one, args=dict(one.args, n_desc=m.n_old - 1)),
+                    dataclasses.replace(one, args=dict(one.args, d0=1))):
+        with pytest.raises(AssertionError):
+            _coverage([planted], m.n_old)
+    with pytest.raises(AssertionError):
+        _coverage([one, one], m.n_old)
 
 
 @pytest.mark.skipif(not os.environ.get("REMP_MODEL_LIMITS"),
@@ -241,6 +284,9 @@ def test_model_size_limits():
 def test_model_full_size_layouts(lo, ln):
     w = synthkv.GQA_70B
     m = km.Migration(w, synthkv.make_inputs(w), lo, ln, data=False, seed=9)
+    _coverage(m.pack_launches(0, 0, w.num_layers), m.n_old)
+    _coverage(m.unpack_launches(0, 0, w.num_layers), m.n_new)
+    _coverage(m.local_launches(0, 0, w.num_layers), m.n_new)
     assert m.pack(0, sample=24) == 0
     assert m.unpack(0, sample=24) == 0
     assert m.copy_local(0, sample=24) == 0
