@@ -769,7 +769,7 @@ __global__ __launch_bounds__(kTileThreads) void copy_local_tiles(const LocalTile
 
 // Between a ROCm pool and one of another layout, with one block size on both sides: copy_strips with the other
 // pool's rows in the place of staging.  A new block holds the tokens of one old block, slot for slot; where the device
-// tables say otherwise nothing is copied and the flag is set.  Bound by HBM.  Measured on MI355X against
+// tables say otherwise the flag is set and each row is looked up (copy_strip_rows).  Bound by HBM.  Measured on MI355X against
 // copy_local_tiles (us with the expansion): 7B MHA ROCm -> NHD 1090 -> 919, NHD -> ROCm 1083 -> 922, 70B GQA ROCm -> NHD
 // 975 -> 803, fp8 NHD -> ROCm 584 -> 479.
 struct LocalStripItem {
@@ -801,6 +801,39 @@ struct LocalStripArgs {
 };
 static_assert(sizeof(LocalStripArgs) < 4096, "local strip kernel arguments must stay below 4 KiB");
 
+template <int EB> struct ElemT;
+template <> struct ElemT<1> { typedef uint8_t type; };
+template <> struct ElemT<2> { typedef uint16_t type; };
+template <> struct ElemT<4> { typedef uint32_t type; };
+
+// A strip of a block whose rows do not lie in one old block slot for slot: every lane takes a column of a row, from wherever
+// that row's source is; rows without one are left alone.
+template <bool TO_ROCM, int EB>
+__device__ __forceinline__ void copy_strip_rows(const LocalStripArgs& a, const LocalUnit<1>& b, uint64_t src0,
+                                                uint64_t dst, uint32_t kv, uint32_t row, uint32_t col) {
+    typedef typename ElemT<EB>::type E;
+    constexpr uint32_t M = kVecBytes / EB;
+    const uint32_t bs = a.old_block_size, j = fast_div(col, a.head_magic, a.head_shift);
+    int32_t block;
+    uint32_t slot;
+    if (row >= static_cast<uint32_t>(b.n) || !find_source(a, b, row, &block, &slot)) return;
+    const uint64_t src =
+        src0 + static_cast<uint64_t>(static_cast<uint32_t>(block)) * static_cast<uint64_t>(a.old_block_stride);
+    const uint32_t at = TO_ROCM ? slot : row, cell_at = TO_ROCM ? row : slot;   // in the other pool, in the ROCm pool
+    const uint64_t line = (TO_ROCM ? src : dst) + static_cast<uint64_t>(at) * a.row_step +
+                          static_cast<uint64_t>(j) * a.head_step + (col - j * a.head_vecs) * kVecBytes;
+    const uint64_t cell = (TO_ROCM ? dst : src) + static_cast<uint64_t>(col) * bs * kVecBytes;
+    if (kv == 0) {
+        const uint64_t k = cell + cell_at * kVecBytes;
+        *(REMP_GLOBAL Vec16*)(TO_ROCM ? k : line) = *(const REMP_GLOBAL Vec16*)(TO_ROCM ? line : k);
+        return;
+    }
+    for (uint32_t e = 0; e < M; ++e) {
+        const uint64_t v = cell + (e * bs + cell_at) * EB;
+        *(REMP_GLOBAL E*)(TO_ROCM ? v : line + e * EB) = *(const REMP_GLOBAL E*)(TO_ROCM ? line + e * EB : v);
+    }
+}
+
 template <bool TO_ROCM, int EB>
 __global__ __launch_bounds__(kMaxStripThreads) void copy_local_strips(const LocalStripArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -815,19 +848,24 @@ __global__ __launch_bounds__(kMaxStripThreads) void copy_local_strips(const Loca
         (const REMP_CONSTANT Int4*)(reinterpret_cast<uint64_t>(a.old_desc)),
         (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(a.tok_off)),
         (const REMP_CONSTANT int32_t*)(reinterpret_cast<uint64_t>(a.old_blk_off)), i, 0);
-    const int32_t on = b.t0 >= 0 && b.q * bs == static_cast<uint32_t>(b.t0) ? b.o.v.n : 0;
-    if (on < b.n && v == 0) *a.flag = kFlagTables;
-    const uint32_t n = static_cast<uint32_t>(min(on, b.n));
+    const bool same = b.t0 >= 0 && b.q * bs == static_cast<uint32_t>(b.t0) && b.o.v.n >= b.n;
+    if (!same && v == 0) *a.flag = kFlagTables;
+    const uint32_t n = static_cast<uint32_t>(b.n);
     const bool tail = s == it.strips - 1;
     const uint32_t cols = tail ? it.last : a.strip, c0 = s * a.strip;
     const uint32_t lrow = (a.strip + 1) * kVecBytes;
-    const uint64_t src = (kv ? it.src_v : it.src_k) +
-                         static_cast<uint64_t>(static_cast<uint32_t>(b.o.v.block)) * static_cast<uint64_t>(a.old_block_stride);
+    const uint64_t src0 = kv ? it.src_v : it.src_k;
+    const uint64_t src = src0 + static_cast<uint64_t>(static_cast<uint32_t>(b.o.v.block)) *
+                                    static_cast<uint64_t>(a.old_block_stride);
     const uint64_t dst = (kv ? it.dst_v : it.dst_k) +
                          static_cast<uint64_t>(static_cast<uint32_t>(b.block)) * static_cast<uint64_t>(a.new_block_stride);
     // in the other pool: column c0 + col of row `row`
     const uint32_t row = fast_div(v, tail ? it.last_magic : a.strip_magic, tail ? it.last_shift : a.strip_shift);
     const uint32_t col = v - row * cols, j = fast_div(c0 + col, a.head_magic, a.head_shift);
+    if (!same) {
+        copy_strip_rows<TO_ROCM, EB>(a, b, src0, dst, kv, row, c0 + col);
+        return;
+    }
     const uint64_t line_at = (TO_ROCM ? src : dst) + static_cast<uint64_t>(row) * a.row_step +
                              static_cast<uint64_t>(j) * a.head_step + (c0 + col - j * a.head_vecs) * kVecBytes;
     // in the ROCm pool, as in copy_strips

@@ -74,15 +74,17 @@ LIMITS = custom(name="limits", num_layers=1, num_kv_heads=1, head_dim=4, elem_by
 # Pool layout pairs (old, new) and new block sizes of the shifted-lengths case: NHD, HND and ROCm tiles,
 # same and mixed, with the old block size (16) kept or doubled.
 SHIFTED_LAYOUTS = [(0, 0, 16), (1, 1, 16), (2, 2, 16), (0, 1, 16), (1, 1, 32), (2, 2, 32), (2, 0, 32)]
+# and those whose rows are copied one by one where the tables disagree, whatever the others of the block do
+SHIFTED_ROWS = [(0, 0, 16), (0, 0, 32), (0, 0, 8), (1, 0, 16), (2, 0, 16), (0, 2, 16), (2, 1, 16), (1, 2, 16)]
 
 
-def shifted_old_lengths_case(new_block_size: int = 16):
+def shifted_old_lengths_case(new_block_size: int = 16, num_seqs: int = 3, head_dim: int = 64):
     """Identity topology (every slice is local) and old device tables that disagree with the host ones:
     17 tokens move from sequence 1 to sequence 0 (same total, shifted starts), and sequence 1's first old
     block is physical block 0.  The local copies combine the new expansion's token offsets with the old
     one's, so the first 16 rows of sequence 1 get a negative token index.  Returns (workload, inputs,
     (device lengths, device row offsets, device block ids))."""
-    w = custom(num_layers=2, num_kv_heads=8, head_dim=64, old_topo=(2, 1), new_topo=(2, 1), num_seqs=3,
+    w = custom(num_layers=2, num_kv_heads=8, head_dim=head_dim, old_topo=(2, 1), new_topo=(2, 1), num_seqs=num_seqs,
                length_law=("fixed", 40), seed=5, new_block_size=new_block_size)
     inp = synthkv.make_inputs(w)
     t = inp.old_tables
@@ -97,3 +99,25 @@ def shifted_old_lengths_case(new_block_size: int = 16):
     else:
         ids[first1] = 0
     return w, inp, (lens, t.offsets.copy(), ids)
+
+
+def sources_by_definition(inp, dev_old):
+    """Per live token of the new tables, where a local copy under the device's old tables finds its row: lists
+    (new block, new slot, old block, old slot); tokens without a source are left out.  A token's place is its
+    index on the token axis less its sequence's first token by the device lengths; it has a source when that lies in
+    a block of the sequence, as far as that block is live."""
+    lens, offs, ids = dev_old
+    t = inp.new_tables
+    bo, bn = inp.old_tables.block_size, t.block_size
+    starts = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    per = (lens.astype(np.int64) + bo - 1) // bo
+    first = np.concatenate([[0], np.cumsum(per)])
+    total = int(((inp.old_tables.seq_lens.astype(np.int64) + bo - 1) // bo).sum())   # descriptors that the plan holds
+    out, tok = [], 0
+    for s in range(len(t.seq_lens)):
+        for i in range(int(t.seq_lens[s])):
+            at = tok + i - int(starts[s])
+            if at >= 0 and at < int(lens[s]) and first[s] + at // bo < total:
+                out.append((int(t.ids[t.offsets[s] + i // bn]), i % bn, int(ids[offs[s] + at // bo]), at % bo))
+        tok += int(t.seq_lens[s])
+    return np.array(out, np.int64).T

@@ -25,7 +25,8 @@ from gpu_harness import (DeviceTables, RankPool, Workspace, log, rank_layers, sh
 
 pytestmark = pytest.mark.gpu
 
-from edgecases import EDGE, SHIFTED_LAYOUTS, custom as _custom, shifted_old_lengths_case
+from edgecases import EDGE, SHIFTED_LAYOUTS, SHIFTED_ROWS, custom as _custom, shifted_old_lengths_case, \
+    sources_by_definition
 
 T = oracle.Topology
 GOLDEN = os.path.join(os.path.dirname(__file__), "golden")
@@ -254,11 +255,28 @@ def test_mismatched_device_tables_are_contained():
 
 @pytest.mark.parametrize("lo,ln,bn", SHIFTED_LAYOUTS)
 def test_local_copy_contains_shifted_device_lengths(lo, ln, bn):
+    _shifted_lengths(lo, ln, bn)
+
+
+@pytest.mark.parametrize("num_seqs,head_dim", [(3, 64), (1030, 8)])
+@pytest.mark.parametrize("lo,ln,bn", SHIFTED_ROWS)
+def test_local_copy_takes_the_rows_that_have_a_source(lo, ln, bn, num_seqs, head_dim):
+    """Under the same tables, every row that has a source is copied from it and every other row is left alone."""
+    w, inp, dev_old, new_host, old_host, got = _shifted_lengths(lo, ln, bn, num_seqs, head_dim)
+    nb, ns, ob, os_ = sources_by_definition(inp, dev_old)
+    for q, per in got.items():
+        for l, a in per.items():
+            want = new_host[q][l].copy()
+            want[:, nb, ns] = old_host[q][l][:, ob, os_]
+            assert np.array_equal(a, want), f"rank {q} layer {l}"
+
+
+def _shifted_lengths(lo, ln, bn, num_seqs=3, head_dim=64):
     """Old device lengths that shift a sequence start (same total) give some rows of the local copies a
     negative token index; those rows must be skipped and flagged, never read from before an old block.
     (The CPU model of the kernels checks this case access by access: test_model_shifted_old_lengths.)"""
     rk = _rk()
-    w, inp, (lens, offs, ids) = shifted_old_lengths_case(bn)
+    w, inp, (lens, offs, ids) = shifted_old_lengths_case(bn, num_seqs, head_dim)
     L = w.num_layers
     plan = rk.Plan(w.old_topo, w.new_topo, shape_of(w), rk.HostTables.of(inp.old_tables))
     old_host = hostpools.source_pools(w, inp.old_tables)
@@ -289,10 +307,13 @@ def test_local_copy_contains_shifted_device_lengths(lo, ln, bn):
     for s_ in range(len(inp.lens)):
         blk, slot = oracle.token_slots(inp.new_tables, s_)
         live[blk, slot] = True
+    pools = {}
     for q in range(W):                    # dead slots of the new pools untouched
+        pools[q] = {}
         for l, (kt, vt) in dst[q][1].items():
-            got = oracle.decode_pool([kt.cpu().numpy().view(nd), vt.cpu().numpy().view(nd)], ln)
+            got = pools[q][l] = oracle.decode_pool([kt.cpu().numpy().view(nd), vt.cpu().numpy().view(nd)], ln)
             assert np.array_equal(got[:, ~live], new_host[q][l][:, ~live]), f"rank {q} layer {l}: a dead slot written"
+    return w, inp, (lens, offs, ids), new_host, old_host, pools
 
 
 # ---------------------------------------------------------------------------

@@ -20,7 +20,8 @@ import oracle
 import synthkv
 
 import kernel_model as km
-from edgecases import EDGE, LIMITS, SHIFTED_LAYOUTS, shifted_old_lengths_case as _shifted_case
+from edgecases import EDGE, LIMITS, SHIFTED_LAYOUTS, SHIFTED_ROWS, shifted_old_lengths_case as _shifted_case, \
+    sources_by_definition
 from fuzzcases import layout_cases, layout_count, random_windows, random_workload, seed_range
 
 T = oracle.Topology
@@ -304,6 +305,21 @@ def test_model_shifted_old_lengths_are_contained(lo, ln, bn):
     m = km.Migration(w, inp, lo, ln, data=True, dev_old=dev_old)
     flags = [m.copy_local(r) for r in range(min(m.old.tp * m.old.pp, m.new.tp * m.new.pp))]
     assert all(f == 1 for f in flags), f"shifted device lengths went unreported: {flags}"
+
+
+@pytest.mark.parametrize("lo,ln,bn", SHIFTED_ROWS)
+def test_model_rows_with_a_source_are_copied(lo, ln, bn):
+    """Under the same tables, every row that has a source is copied from it and every other row is left alone."""
+    w, inp, dev_old = _shifted_case(bn)
+    m = km.Migration(w, inp, lo, ln, data=True, dev_old=dev_old)
+    assert m.copy_local(0) == 1
+    nb, ns, ob, os_ = sources_by_definition(inp, dev_old)
+    assert 0 < nb.size < int(inp.lens.sum())
+    got = m.new_pools()[0]
+    for l, want in m.new_host[0].items():
+        want = want.copy()
+        want[:, nb, ns] = m.old_host[0][l][:, ob, os_]
+        assert np.array_equal(got[l], want), f"layer {l}"
 
 
 def test_model_out_of_range_ids_are_contained():
