@@ -38,8 +38,8 @@ constexpr uint64_t kPeerMinBytes = 2048, kPeerEndBytes = 4096;
 struct TileItem {
     uint64_t paged_k, paged_v;   // the slice's first head tile of the layer's block 0
     uint64_t stage;              // first byte of the slice in its staging buffer (K part)
-    uint32_t row_bytes;          // heads * head_bytes: a staging row
-    uint32_t heads;              // heads in the slice
+    uint32_t row_bytes;          // a staging row
+    uint32_t heads;              // heads in the slice, or in the part of it that this item is
     uint32_t strips;             // strips per block (copy_strips)
     uint32_t last;               // columns of a block's last strip (copy_strips)
     uint32_t unit;               // vectors per unit (copy_head_rows)
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kRunThreads) void copy_head_rows(const TileArgs a) 
     if (!pick_tile<N>(a.desc, a.n_desc, pos * kRunThreads, threadIdx.x & 63u, it, heads, &d, &r, &j)) return;
     if (PACK) {
         row = fast_div(r, it.row_magic, it.row_shift);
-        c = r - row * (it.row_bytes / kVecBytes);
+        c = r - row * it.heads * (hb / kVecBytes);
         j = fast_div(c, a.head_magic, a.head_shift);
         c -= j * (hb / kVecBytes);
     } else {

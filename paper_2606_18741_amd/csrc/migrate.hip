@@ -46,6 +46,10 @@ static thread_local hipEvent_t g_trace_stop = nullptr;
 // Bound on the vectors of one unit.
 constexpr uint64_t kMaxUnitVectors = uint64_t(1) << 31;
 
+// Head tiles: slices with more vectors than this in a block go by ranges of heads, so that a launch can number a block's
+// (units_per_launch).  1 GiB of one block: no layout in use comes near.
+constexpr uint64_t kMaxTileVectors = uint64_t(1) << 26;
+
 // A dispatch counts its work-items in 32 bits per grid dimension.
 static remp_status check_grid(int64_t gx, int64_t gy, int threads, const char* what) {
     if (gx * threads >= (int64_t(1) << 32) || gx * gy >= (int64_t(1) << 32))
@@ -384,6 +388,13 @@ static uint32_t layer_slices(const std::vector<HostSlice>& slices) {
     return static_cast<uint32_t>(n);
 }
 
+// Calls add(first head, heads) for the ranges of `heads` heads that have at most kMaxTileVectors in a block, `tile` each.
+template <typename F>
+static void head_ranges(uint32_t heads, uint64_t tile, const F& add) {
+    const uint32_t most = static_cast<uint32_t>(std::max<uint64_t>(1, kMaxTileVectors / tile));
+    for (uint32_t h = 0; h < heads; h += most) add(h, std::min(most, heads - h));
+}
+
 template <bool PACK>
 static remp_status launch_tile_groups(const remp_kv_plan_t& p, const std::vector<HostSlice>& slices, int64_t n_desc,
                                       int32_t bs, int64_t block_stride, int32_t max_hc, const char* ws,
@@ -437,13 +448,23 @@ static remp_status launch_tile_groups(const remp_kv_plan_t& p, const std::vector
 }
 
 template <bool PACK>
-static remp_status launch_tiles(const remp_kv_plan_t& p, const std::vector<HostSlice>& slices, int64_t n_desc,
+static remp_status launch_tiles(const remp_kv_plan_t& p, const std::vector<HostSlice>& whole, int64_t n_desc,
                                 int32_t bs, int64_t block_stride, int32_t layout, const char* ws, int64_t desc_off,
                                 const StampCheck& check, hipStream_t stream) {
-    if (slices.empty() || n_desc == 0) return REMP_OK;
+    if (whole.empty() || n_desc == 0) return REMP_OK;
     if (n_desc >= (int64_t(1) << 30)) return fail(REMP_E_UNSUPPORTED, "more than 2^30 live blocks in one call");
     const int32_t eb = p.shape.elem_bytes;
     const int64_t hb = static_cast<int64_t>(p.shape.head_dim) * eb;
+    std::vector<HostSlice> slices;
+    for (const HostSlice& s : whole)
+        head_ranges(static_cast<uint32_t>(s.head_count), static_cast<uint64_t>(bs) * hb / kVecBytes, [&](uint32_t h, uint32_t n) {
+            HostSlice part = s;
+            part.paged_k += static_cast<uint64_t>(h) * bs * hb;
+            part.paged_v += static_cast<uint64_t>(h) * bs * hb;
+            part.stage += static_cast<uint64_t>(h) * hb;
+            part.head_count = static_cast<int32_t>(n);
+            slices.push_back(part);
+        });
     uint64_t bits = static_cast<uint64_t>(block_stride) | static_cast<uint64_t>(hb);
     uint32_t max_hc = 1;
     for (const HostSlice& s : slices) {
@@ -867,7 +888,7 @@ static void launch_local_strips_t(const LocalStripArgs& a, dim3 grid, int thread
 }
 
 // Local copy between a ROCm pool and one of another layout, block sizes equal (copy_local_strips).
-static remp_status launch_local_strips(const remp_kv_plan_t& p, const std::vector<HostLocal>& items, uint32_t strip,
+static remp_status launch_local_strips(const remp_kv_plan_t& p, const std::vector<HostLocal>& whole, uint32_t strip,
                                        uint32_t max_cols, int32_t old_layout, int32_t new_layout, const char* ws,
                                        const StampCheck& check, hipStream_t stream) {
     const remp_kv_shape& sh = p.shape;
@@ -878,6 +899,14 @@ static remp_status launch_local_strips(const remp_kv_plan_t& p, const std::vecto
     const int64_t orow = p.own_old.heads_per_rank() * hb, nrow = p.own_new.heads_per_rank() * hb;
     const bool to_rocm = new_layout == kLayoutRocmSplit;
     const int32_t other = to_rocm ? old_layout : new_layout;
+    const uint64_t ostep = old_layout == kLayoutNHD ? hb : hb * bs, nstep = new_layout == kLayoutNHD ? hb : hb * bs;
+    std::vector<HostLocal> items;
+    for (const HostLocal& h : whole)
+        head_ranges(static_cast<uint32_t>(h.row_bytes / hb), static_cast<uint64_t>(bs) * hb / kVecBytes, [&](uint32_t first, uint32_t n) {
+            items.push_back(HostLocal{h.src_k + first * ostep, h.src_v + first * ostep, h.dst_k + first * nstep,
+                                      h.dst_v + first * nstep, static_cast<uint32_t>(n * hb)});
+        });
+    max_cols = std::min<uint32_t>(max_cols, static_cast<uint32_t>(std::max<uint64_t>(hb / kVecBytes, kMaxTileVectors / bs)));
     const auto set = [](auto* magic, auto* shift, uint32_t divisor) {
         const FastDiv f = make_fastdiv(divisor);
         *magic = f.magic;

@@ -101,6 +101,31 @@ def test_dispatch_is_reached():
     assert any(a == b for a, b in strips) and any(a == 8 < b for a, b in strips) and any(b % a for a, b in strips)
 
 
+@pytest.mark.parametrize("layout,other", [(km.HND, km.HND), (km.ROCM, km.ROCM), (km.ROCM, km.NHD), (km.NHD, km.ROCM)])
+def test_blocks_that_one_launch_cannot_number(layout, other):
+    """A slice of 2^31 vectors in each block: more than a dispatch counts work-items for, with K and V.  It goes by ranges
+    of heads that adjoin, and every launch has blocks to copy."""
+    heads, hb, bs = 1 << 26, 16, 32
+    w = custom(num_layers=1, num_kv_heads=heads, head_dim=hb, elem_bytes=1, old_block_size=bs, new_block_size=bs,
+               old_topo=(1, 1), new_topo=(1, 1), num_seqs=2, length_law=("fixed", 1))
+    m = km.Migration(w, synthkv.make_inputs(w), layout, other, data=False)
+    calls = [m.local_launches(0, 0, 1)] if layout != other else [m.pack_launches(0, 0, 1), m.unpack_launches(0, 0, 1)]
+    for launches in calls:
+        assert all(x.args.get("n_desc", x.args.get("n_new")) == 2 for x in launches)
+        parts = [i for x in launches for i in x.args["items"]]
+        n = [getattr(i, "head_count", i.row_bytes // hb) for i in parts]
+        assert sum(n) == heads and max(n) * bs <= km.MAX_TILE_VECTORS
+        for at, lay, row in (("src_k", layout, hb), ("dst_k", other, hb), ("paged_k", other, hb), ("stage", km.NHD, hb)):
+            if hasattr(parts[0], at):
+                step = row if lay == km.NHD else row * bs
+                assert all(getattr(b, at) - getattr(a, at) == k * step for a, b, k in zip(parts, parts[1:], n))
+    if layout != other:
+        m.copy_local(0, sample=16)
+    else:
+        m.pack(0, sample=16)
+        m.unpack(0, sample=16)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(CASES))
 def test_gpu(name):
