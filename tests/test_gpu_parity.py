@@ -231,10 +231,12 @@ def test_unpack_from_oracle_staging():
             np.testing.assert_array_equal(got[l], new_host[q][l])
 
 
-def test_mismatched_device_tables_are_contained():
-    """Device tables that disagree with the host ones must not fault; the flag reports it."""
+@pytest.mark.parametrize("num_seqs", [3, 1030])
+def test_mismatched_device_tables_are_contained(num_seqs):
+    """Device tables that disagree with the host ones must not fault; the flag reports it, by the expansion of few
+    blocks and by that of many sequences."""
     rk = _rk()
-    w = synthkv.reduced(synthkv.TINY, num_seqs=3, max_len=60)
+    w = synthkv.reduced(synthkv.TINY, num_seqs=num_seqs, max_len=60 if num_seqs == 3 else 20)
     inp = synthkv.make_inputs(w)
     plan = rk.Plan(w.old_topo, w.new_topo, shape_of(w), rk.HostTables.of(inp.old_tables))
     old_host = hostpools.source_pools(w, inp.old_tables)

@@ -307,11 +307,14 @@ def test_model_shifted_old_lengths_are_contained(lo, ln, bn):
     assert all(f == 1 for f in flags), f"shifted device lengths went unreported: {flags}"
 
 
+@pytest.mark.parametrize("num_seqs,head_dim", [(3, 64), (1030, 8)])
 @pytest.mark.parametrize("lo,ln,bn", SHIFTED_ROWS)
-def test_model_rows_with_a_source_are_copied(lo, ln, bn):
-    """Under the same tables, every row that has a source is copied from it and every other row is left alone."""
-    w, inp, dev_old = _shifted_case(bn)
+def test_model_rows_with_a_source_are_copied(lo, ln, bn, num_seqs, head_dim):
+    """Under the same tables, every row that has a source is copied from it and every other row is left alone, whichever
+    kernel expands them (1030 sequences are more than one workgroup takes)."""
+    w, inp, dev_old = _shifted_case(bn, num_seqs, head_dim)
     m = km.Migration(w, inp, lo, ln, data=True, dev_old=dev_old)
+    assert km.takes_expand_small(m.S, m.n_new) == (num_seqs == 3)
     assert m.copy_local(0) == 1
     nb, ns, ob, os_ = sources_by_definition(inp, dev_old)
     assert 0 < nb.size < int(inp.lens.sum())
@@ -322,8 +325,9 @@ def test_model_rows_with_a_source_are_copied(lo, ln, bn):
         assert np.array_equal(got[l], want), f"layer {l}"
 
 
-def test_model_out_of_range_ids_are_contained():
-    w = synthkv.reduced(synthkv.TINY, num_seqs=3, max_len=60)
+@pytest.mark.parametrize("num_seqs", [3, 1030])
+def test_model_out_of_range_ids_are_contained(num_seqs):
+    w = synthkv.reduced(synthkv.TINY, num_seqs=num_seqs, max_len=60 if num_seqs == 3 else 20)
     inp = synthkv.make_inputs(w)
     t = inp.old_tables
     dev_old = (t.seq_lens, t.offsets, np.full_like(t.ids, 1 << 30))
