@@ -213,10 +213,11 @@ enum {
  * fewer than 2^28 live blocks in either block size (REMP_E_UNSUPPORTED).  On
  * failure *out is NULL.
  * Tuning hook (measurement only): if the environment variable
- * REMP_KV_WG_BYTES holds a positive integer when the plan is created, the copy
- * kernels launched with this plan aim to move about that many bytes per
- * workgroup instead of the built-in per-kernel targets (capped at 1 GiB; pack
- * and unpack of NHD pools take 1 to 16 KiB).  It
+ * REMP_KV_WG_BYTES holds a positive integer when the plan is created, the
+ * workgroups that copy NHD rows with this plan (pack, unpack and local copy,
+ * but not shares that follow one another in the grid or rows in pieces) take
+ * about that many bytes, 1 to 16 KiB, instead of the built-in number; other
+ * layouts do not heed it.  It
  * changes launch shapes only, never the bytes written; later changes of the
  * environment do not affect an existing plan. */
 REMP_API remp_status remp_kv_plan(const remp_topo* old_topo, const remp_topo* new_topo,

@@ -340,12 +340,12 @@ def test_local_fast_path_windows():
     check_against_oracle(w, synthkv.make_inputs(w), windows=[(0, 13), (13, 40), (40, 80)], local=True)
 
 
-@pytest.mark.parametrize("wg_bytes", [2048, 8192, 32768, 262144, 1 << 20])
+@pytest.mark.parametrize("wg_bytes", [1024, 2048, 4096, 8192, 1 << 20])
 @pytest.mark.parametrize("name", ["mha7b", "gqa70b", "merged_rows_mha"])
 def test_workgroup_sizes(name, wg_bytes, monkeypatch):
-    """Bit-exact at other bytes-per-workgroup targets (REMP_KV_WG_BYTES, a tuning override): one to
-    many units per workgroup and ragged last workgroups, for the small-unit (GQA) and large-unit (MHA)
-    launch shapes, staged and with the local fast path."""
+    """Bit-exact at other bytes per workgroup (REMP_KV_WG_BYTES, a tuning override): one wave to the 16 that a
+    workgroup holds at most, ragged last workgroups, small (GQA) and large (MHA) units, staged and with the local
+    fast path."""
     w = EDGE[name] if name in EDGE else synthkv.reduced(synthkv.WORKLOADS[name], num_seqs=4, max_len=250)
     monkeypatch.setenv("REMP_KV_WG_BYTES", str(wg_bytes))
     inp = synthkv.make_inputs(w)
@@ -586,10 +586,30 @@ def test_reuse_without_expansion_copies_nothing_hnd():
     _reuse_stale_case("random", layout=1)
 
 
-def _reuse_stale_case(fill, layout):
+ODD_SPLIT = dict(num_kv_heads=4, head_dim=100, elem_bytes=1)      # rows of two 100-byte shares
+
+
+@pytest.mark.parametrize("lo,ln,w,kernels", [
+    (2, 2, None, {"copy_strips", "copy_local_tiles"}), (2, 0, None, {"copy_strips", "copy_runs", "copy_local_strips"}),
+    (0, 2, None, {"copy_strips", "copy_runs", "copy_local_strips"}),
+    (0, 0, _custom(old_topo=(2, 1), new_topo=(4, 1), **ODD_SPLIT), {"copy_pieces", "copy_runs", "copy_local"}),
+    (0, 0, _custom(old_topo=(4, 1), new_topo=(2, 1), **ODD_SPLIT), {"copy_runs", "copy_pieces", "copy_local"}),
+    (2, 2, _custom(num_kv_heads=2, head_dim=72, new_topo=(2, 1)), {"copy_tile_groups", "copy_local_tiles"})])
+def test_reuse_without_expansion_copies_nothing_other_kernels(lo, ln, w, kernels):
+    """The same for the strips and tile groups of ROCm pools and for rows in pieces."""
+    _reuse_stale_case("random", lo, ln, w, kernels)
+
+
+def _reuse_stale_case(fill, layout, new_layout=None, w=None, kernels=None):
     """A reusing call on a workspace that holds no matching descriptors copies nothing and sets flag 2."""
     rk = _rk()
-    w = synthkv.reduced(synthkv.TINY, num_seqs=4, max_len=120)
+    new_layout = layout if new_layout is None else new_layout
+    w = w or synthkv.reduced(synthkv.TINY, num_seqs=4, max_len=120)
+    if kernels:
+        import kernel_model as km
+        m = km.Migration(w, synthkv.make_inputs(w), layout, new_layout, data=False)
+        calls = m.pack_launches(0, 0, m.L) + m.unpack_launches(0, 0, m.L) + m.local_launches(0, 0, m.L)
+        assert {x.kernel for x in calls} == kernels
     inp = synthkv.make_inputs(w)
     L = w.num_layers
     plan, old_host, new_host, src, dst, pairs, staging = _reuse_setup(w, inp)
@@ -605,8 +625,8 @@ def _reuse_stale_case(fill, layout):
     reuse = rk.REMP_KV_REUSE_DESCRIPTORS
     # the same storage read as `layout` (HND selects the head-tile kernels; nothing may be written anyway)
     src_arg = rk.PoolArg(list(src[0].arg._k), list(src[0].arg._v), inp.old_tables.num_blocks, layout=layout)
-    dst_arg = rk.PoolArg(list(dst[0].arg._k), list(dst[0].arg._v), inp.new_tables.num_blocks, layout=layout)
-    log(f"[reuse] no expansion, workspace {fill}, layout {layout}")
+    dst_arg = rk.PoolArg(list(dst[0].arg._k), list(dst[0].arg._v), inp.new_tables.num_blocks, layout=new_layout)
+    log(f"[reuse] no expansion, workspace {fill}, layouts {layout} {new_layout}")
     plan.pack(0, src_arg, dto.dev, window_args(plan, staging, 0, plan.info.new_world, True, 0, L), ws.buf,
               ws.bytes, stream_handle(), flags=reuse)
     torch.cuda.synchronize()
