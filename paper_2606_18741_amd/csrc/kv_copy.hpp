@@ -104,8 +104,8 @@ struct LocalItem {
     uint64_t src_k, src_v;   // old storage of the layer, offset to the slice's first head
     uint64_t dst_k, dst_v;   // new storage of the layer, offset to the slice's first head
     uint32_t row_bytes;
-    uint32_t vpr_magic;      // fast division by vectors per row
-    uint32_t vpu;            // vectors per (new block, K or V) unit
+    uint32_t vpr_magic;      // fast division by words per row
+    uint32_t vpu;            // words per (new block, K or V) unit
     uint32_t vpu_magic;
     uint16_t vpr_shift;
     uint16_t vpu_shift;

@@ -235,9 +235,9 @@ __global__ __launch_bounds__(256) void sort_scatter(const BlockDesc* __restrict_
 
 // expand_scan, expand_emit and, with bucket, sort_scan and sort_scatter in one launch, for at most kSmallSeqs sequences
 // and kSmallBlocks live blocks: the offsets and the bucket counters stay in LDS.  Bound by latency: each launch that it
-// saves takes 2-5 us, and every 1024 blocks take one workgroup 2 us more.  Measured on MI355X (us a call pair): eight
-// ranks' calls over 30 blocks 63.5 -> 36.4, pack and unpack of 150 blocks 86.2 -> 81.0, and the local copy of 9,200,
-// where the many workgroups are the better ones, 1021 -> 1036.
+// saves takes 2-5 us, and every 1024 blocks take one workgroup 6-7 us more a call pair.  Measured on MI355X (us, pack and
+// unpack, by several launches / by this one): 64 blocks 33.4 / 19.4, 512 33.6 / 21.8, 1024 33.6 / 28.1, 2048 45.5 / 41.6, 3072 56.9 /
+// 54.5, 4096 67.8 / 69.0, 6000 86.8 / 92.7, 9000 118.6 / 133.2.
 constexpr int32_t kSmallSeqs = kScanThreads;
 constexpr int64_t kSmallBlocks = 4096;
 constexpr int kSmallBuckets = kSmallBlocks / kDescsPerBucket;

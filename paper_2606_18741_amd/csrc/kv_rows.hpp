@@ -42,8 +42,12 @@ enum RowsOrder { kBySlice, kByRow, kByShare };   // kBySlice: not here, each sli
 //           2 x 2 KiB 5.55 / 5.92 / 6.32   2 x 4 KiB 6.57 / 6.14 / 6.68
 //           4 x 128 B 5.81 / 6.04 / 5.59   4 x 256 B 5.73 / 6.09 / 5.59   4 x 512 B 6.16 / 6.10 / 5.82
 //           4 x 1 KiB 5.59 / 5.83 / 6.20   4 x 2 KiB 5.68 / 5.92 / 6.30
+// and three shares (us):
+//   pack    3 x 64 B 1399 / 946 / 1421   3 x 256 B 920 / 917 / 910   3 x 512 B 870 / 887 / 873   3 x 2 KiB 722 / 748 / 727
+//   unpack  3 x 64 B 1250 / 961 / 1143   3 x 256 B 997 / 902 / 910   3 x 512 B 908 / 859 / 869   3 x 2 KiB 744 / 713 / 721
 // So: packs with three or four shares by row; rows of 4 KiB and more by share; rows of three or four shares
-// of up to 256 B unpacked by row; the rest by slice.  Shares that are not whole vectors go by copy_pieces, or by row if
+// of up to 256 B unpacked by row; the rest by slice (of three shares of 512 B to 1 KiB that costs 4-6% unpacked, and by row 1-3%
+// packed).  Shares that are not whole vectors go by copy_pieces, or by row if
 // they are less than a vector: by slice each would write parts of the same 64-byte sectors at different times.
 constexpr uint32_t kByShareMinRow = 4096;
 constexpr uint32_t kUnpackByRowMaxShare = 256;

@@ -30,9 +30,10 @@ constexpr int kStripLanes = 256;           // lanes of a strip (copy_strips), wh
 constexpr int kMaxStripThreads = 1024;     // and at most: one column of the largest block
 
 // Slices of one layer that hold 2-4 KiB of each block are copied side by side, block by block: one after another,
-// each pass writes (or reads) every other 2 KiB of the pool, which the memory takes 11% slower (MI355X, 70B
-// GQA fp8, two sources' 2 KiB head tiles: HND unpack 5.42 -> 6.04 TB/s, ROCm 5.45 -> 5.95).  Larger pieces are
-// no faster so (two of 4 KiB: 6.23 -> 6.12 TB/s), and pieces of 1.25 KiB lose 6%.
+// each pass writes (or reads) every other 2 KiB of the pool, which the memory takes slower (MI355X, 70B
+// GQA fp8, two sources' 2 KiB head tiles, pack and unpack, us one after another / side by side: HND 2100 / 1968, ROCm 2114 / 2022;
+// 3 KiB ROCm 1222 / 1199; over less memory, 2 to 3.5 KiB, 0-1% either way).  Larger pieces are
+// no faster so (two of 4 KiB: 1926 / 1943), and pieces of 1.25 KiB lose 2-6%.
 constexpr uint64_t kPeerMinBytes = 2048, kPeerEndBytes = 4096;
 
 struct TileItem {
@@ -308,8 +309,9 @@ __global__ __launch_bounds__(kMaxStripThreads) void copy_strips(const TileArgs a
 
 // ROCm tiles whose strip would be a whole row of a few columns that leaves many lanes of its waves idle
 // (strips_fill): a workgroup of 256 lanes takes several (block, K or V, head) tiles, 16 KiB, vector
-// after vector, through LDS.  Strips are slower there (MI355X, one head a rank, pack / unpack: 72 of 128 lanes 5.0 /
-// 5.35 TB/s so, 4.4 / 4.25 by strips; 144 of 192 5.45 / 5.4 and 5.25 / 5.05; 160 of 192 5.8 / 5.6 and 5.6 / 5.35).
+// after vector, through LDS.  Measured on MI355X, one fp8 head a rank, blocks of 16 (us by strips / so, pack and unpack): of the
+// strip's lanes 62% busy 448 / 421 and 238 / 208, 75% 396 / 414 and 221 / 218 (of 192 lanes 403 / 403 and 217 / 204), 81% 365 / 375 and
+// 196 / 197, 83% 380 / 385 and 206 / 202, 87% 362 / 417 and 200 / 212, 92% 367 / 395 and 198 / 204, 94% 356 / 395 and 189 / 196.
 struct GroupItem {
     uint64_t paged_k, paged_v, stage;   // as TileItem
     uint32_t row_bytes;

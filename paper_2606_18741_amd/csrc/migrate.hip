@@ -716,7 +716,8 @@ static remp_status check_pool(const remp_kv_plan_t* plan, const remp_kv_pool* po
 }
 
 // A (block, head) tile of block_size rows of head_dim * elem_bytes bytes, each padded by 16 bytes, must fit
-// the head-tile kernels' LDS budget; checked with the other arguments, before anything is enqueued.
+// the head-tile kernels' LDS budget; checked with the other arguments, before anything is enqueued.  Pack and unpack of HND pools
+// need no LDS, but the header states the limit for both layouts, and the local copy between layouts needs it.
 static remp_status check_tile_fits(const remp_kv_plan_t* plan, int32_t block_size, const char* what) {
     const int64_t hb = static_cast<int64_t>(plan->shape.head_dim) * plan->shape.elem_bytes;
     if (static_cast<int64_t>(block_size) * (hb + 16) > kTileLdsBytes)
@@ -848,9 +849,9 @@ static remp_status collect_slices(const remp_kv_plan_t& p, bool pack, int32_t ra
 
 // In an HND pool the rows of one head's tile are contiguous and in token
 // order, so a slice of a single head has the staging slice's byte order: it is
-// copied like an NHD slice whose rows are one head long.  Used for pack (A/B
-// on MI355X, 70B GQA share with HND pools: pack -4.3% time against the LDS
-// tile kernel); the unpack keeps the tile kernel (+1.2% with the direct copy).
+// copied like an NHD slice whose rows are one head long.  Used for pack.  Measured on MI355X against copy_head_rows (us, so / by it):
+// 256-byte rows in blocks of 16 1033 / 1040, of 64 1024 / 1037, of 1 521 / 529, 512 bytes 1023 / 1038, 1152 bytes 997 / 1014; only 160
+// bytes in blocks of 20, which end inside lines, 1130 / 1084.  Unpacked the two are as close (529 / 534; 160 bytes 594 / 562).
 static bool hnd_single_heads(int32_t layout, const std::vector<HostSlice>& slices) {
     if (layout != kLayoutHND) return false;
     for (const HostSlice& s : slices)
