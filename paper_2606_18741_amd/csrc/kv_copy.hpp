@@ -1,4 +1,4 @@
-// The pack / unpack copy kernel (copy_runs) and the NHD local copy (copy_local).
+// The pack / unpack copy kernel (copy_runs) and the NHD local copies (copy_local, copy_local_tokens).
 // Included by migrate.hip only (one translation unit holds every kernel).
 #pragma once
 
@@ -292,6 +292,57 @@ __global__ __launch_bounds__(kMaxRunThreads) void copy_local(const LocalArgs arg
 #pragma unroll
     for (int k = 0; k < K; ++k)
         if (left[k]) word[k].store(dst[k], left[k]);
+}
+
+// The same for new blocks of one token, of aligned rows of 256 to 511 bytes: a wave of copy_local meets four blocks, whose
+// look-ups cost more than its 1 KiB.  Here it takes 4 KiB: each lane looks up one of its rows, and the lanes that
+// move a row's vectors get its two addresses from that lane.  Bound by HBM and the look-ups' latency.  Measured on MI355X (us,
+// rows resolved into LDS / copy_local / so), 256-byte rows: blocks of 16 to 1, 1.8 GB, 377 / 410 / 372; 0.45 GB 120 / 126 / 118;
+// blocks of 1 122 / 133 / 123.  One wave to a workgroup instead of four 391, two vectors a lane 416; rows of 64 bytes
+// are faster by copy_local (183 / 194), and so are rows of 512 (97).
+constexpr int kTokenThreads = 256, kTokenVectors = 4;
+constexpr uint32_t kTokenMinRow = 256, kTokenEndRow = 512;
+
+__global__ __launch_bounds__(kMaxRunThreads) void copy_local_tokens(const LocalArgs args) {
+    constexpr int K = kTokenVectors;
+    if (stale_descriptors(args.check)) return;
+    const LocalItem& it = args.items[blockIdx.y];
+    const uint32_t kv = blockIdx.z, lane = threadIdx.x & 63u, w0 = wave_first(args.xcd) * K;
+    const uint32_t vpr = it.vpu;
+    const uint32_t u0 = fast_div(w0, it.vpu_magic, it.vpu_shift), u = u0 + lane;
+    const uint32_t end = min(fast_div(w0 + 64 * K - 1, it.vpu_magic, it.vpu_shift), args.n_new_desc - 1);   // the last one
+    const LocalUnit<1> x = load_local_unit<1>(args, reinterpret_cast<const Int4*>(args.new_desc),
+                                              reinterpret_cast<const Int4*>(args.old_desc), args.tok_off,
+                                              args.old_blk_off, min(u, end), 0);
+    uint64_t src = 0, dst = 0;
+    if (u <= end && x.n > 0) {
+        int32_t block;
+        uint32_t slot;
+        if (find_source(args, x, 0, &block, &slot)) {
+            src = (kv ? it.src_v : it.src_k) +
+                  static_cast<uint64_t>(static_cast<uint32_t>(block)) * static_cast<uint64_t>(args.old_block_stride) +
+                  static_cast<uint64_t>(slot) * args.old_row_stride;
+            dst = (kv ? it.dst_v : it.dst_k) +
+                  static_cast<uint64_t>(static_cast<uint32_t>(x.block)) * static_cast<uint64_t>(args.new_block_stride);
+        } else {
+            *args.flag = kFlagTables;
+        }
+    }
+    Vec16 val[K];
+    uint64_t to[K];
+    bool on[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t w = w0 + k * 64 + lane, t = fast_div(w, it.vpu_magic, it.vpu_shift);
+        const uint32_t off = (w - t * vpr) * kVecBytes;
+        const uint64_t from = __shfl(src, static_cast<int>(t - u0), 64);
+        to[k] = __shfl(dst, static_cast<int>(t - u0), 64) + off;
+        on[k] = from != 0;
+        if (on[k]) val[k] = __builtin_nontemporal_load((const REMP_GLOBAL Vec16*)(from + off));
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (on[k]) __builtin_nontemporal_store(val[k], (REMP_GLOBAL Vec16*)to[k]);
 }
 
 }  // namespace remp

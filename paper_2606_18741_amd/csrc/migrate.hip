@@ -1073,10 +1073,11 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
     const int64_t orow = p.own_old.heads_per_rank() * hrow, nrow = p.own_new.heads_per_rank() * hrow;
     const int32_t bo = sh.old_block_size, bn = sh.new_block_size;
     uint64_t bits = static_cast<uint64_t>(orow) | static_cast<uint64_t>(nrow);
-    uint32_t max_row = 0;
+    uint32_t max_row = 0, min_row = items[0].row_bytes;
     for (const HostLocal& it : items) {
         bits |= it.src_k | it.src_v | it.dst_k | it.dst_v | it.row_bytes;
         max_row = std::max(max_row, it.row_bytes);
+        min_row = std::min(min_row, it.row_bytes);
     }
     // Rows that are not whole vectors (MI355X, us; before: rows resolved into LDS, aligned words): 200 of 400 bytes in
     // blocks of 20, before 719, 8-byte words (4 to a lane) 690, any 779; in blocks of 64 706 / 666 / 757; blocks of 64 to
@@ -1086,10 +1087,11 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
     const uint32_t word = vec ? vec : kVecBytes;   // bytes of a word
     const auto vectors = [&](uint32_t row) { return static_cast<uint64_t>(bn) * ((row + word - 1) / word); };
     const uint64_t max_vpu = vectors(max_row);
-    const uint32_t words = vec != 8 ? 1 : max_vpu >= 64 * kLocalWords ? kLocalWords : 2;   // words of a lane
+    const bool tokens = bn == 1 && !odd && min_row >= kTokenMinRow && max_row < kTokenEndRow;   // copy_local_tokens
+    const uint32_t words = tokens ? kTokenVectors : vec != 8 ? 1 : max_vpu >= 64 * kLocalWords ? kLocalWords : 2;   // of a lane
     if (bn > kMaxLocalRows) return fail(REMP_E_UNSUPPORTED, "new block size above the local-copy row limit");
     if (max_vpu >= kMaxUnitVectors) return fail(REMP_E_UNSUPPORTED, "a block of one slice exceeds 2^31 vectors");
-    const int threads = run_threads(p, kRunThreads);
+    const int threads = run_threads(p, tokens ? kTokenThreads : kRunThreads);
 
     LocalArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -1145,6 +1147,11 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
             a.n_new_desc = static_cast<uint32_t>(std::min<int64_t>(per_launch, n_desc - d0));
             const uint64_t wgs = (a.n_new_desc * max_vpu + threads * words - 1) / (threads * words);
             const dim3 grid(static_cast<uint32_t>(a.xcd ? xcd_grid(wgs) : wgs), static_cast<uint32_t>(cnt), 2);
+            if (tokens) {
+                hipLaunchKernelGGL(copy_local_tokens, grid, dim3(threads), 0, stream, a);
+                if (remp_status st = hip_check(hipGetLastError(), "copy_local_tokens launch")) return st;
+                continue;
+            }
             switch (n) {
                 case 1:
                     if (m == 1) launch_local_n<1, 1>(a, grid, threads, vec, words, stream);

@@ -75,7 +75,7 @@ LIMITS = custom(name="limits", num_layers=1, num_kv_heads=1, head_dim=4, elem_by
 # same and mixed, with the old block size (16) kept or doubled.
 SHIFTED_LAYOUTS = [(0, 0, 16), (1, 1, 16), (2, 2, 16), (0, 1, 16), (1, 1, 32), (2, 2, 32), (2, 0, 32)]
 # and those whose rows are copied one by one where the tables disagree, whatever the others of the block do
-SHIFTED_ROWS = [(0, 0, 16), (0, 0, 32), (0, 0, 8), (1, 0, 16), (2, 0, 16), (0, 2, 16), (2, 1, 16), (1, 2, 16)]
+SHIFTED_ROWS = [(0, 0, 16), (0, 0, 32), (0, 0, 8), (0, 0, 1), (1, 0, 16), (2, 0, 16), (0, 2, 16), (2, 1, 16), (1, 2, 16)]
 
 
 def shifted_old_lengths_case(new_block_size: int = 16, num_seqs: int = 3, head_dim: int = 64):

@@ -260,7 +260,7 @@ def test_local_copy_contains_shifted_device_lengths(lo, ln, bn):
     _shifted_lengths(lo, ln, bn)
 
 
-@pytest.mark.parametrize("num_seqs,head_dim", [(3, 64), (1030, 8)])
+@pytest.mark.parametrize("num_seqs,head_dim", [(3, 64), (3, 40), (1030, 8)])
 @pytest.mark.parametrize("lo,ln,bn", SHIFTED_ROWS)
 def test_local_copy_takes_the_rows_that_have_a_source(lo, ln, bn, num_seqs, head_dim):
     """Under the same tables, every row that has a source is copied from it and every other row is left alone."""

@@ -308,7 +308,7 @@ def test_model_shifted_old_lengths_are_contained(lo, ln, bn):
     assert all(f == 1 for f in flags), f"shifted device lengths went unreported: {flags}"
 
 
-@pytest.mark.parametrize("num_seqs,head_dim", [(3, 64), (1030, 8)])
+@pytest.mark.parametrize("num_seqs,head_dim", [(3, 64), (3, 40), (1030, 8)])
 @pytest.mark.parametrize("lo,ln,bn", SHIFTED_ROWS)
 def test_model_rows_with_a_source_are_copied(lo, ln, bn, num_seqs, head_dim):
     """Under the same tables, every row that has a source is copied from it and every other row is left alone, whichever

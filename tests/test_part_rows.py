@@ -32,7 +32,8 @@ CASES = {f"{hb}_{bs}{'_back' if back else ''}": _parts(hb, bs, back=back) for hb
 
 # (head bytes, old block, new block): rows from one old block, two, many; waves that meet one new block to many
 BLOCKS = ((256, 64, 20), (256, 16, 1), (256, 1, 16), (512, 3, 64), (1024, 16, 128), (64, 16, 64), (64, 64, 16), (64, 2, 2),
-          (16, 8, 8), (16, 16, 1), (16, 16, 64), (16, 16, 96), (128, 1, 1), (200, 64, 20), (200, 20, 64), (72, 7, 5), (100, 3, 40), (33, 16, 4), (36, 32, 16), (256, 16, 16), (200, 20, 20), (64, 4, 4))
+          (16, 8, 8), (16, 16, 1), (16, 16, 64), (16, 16, 96), (128, 1, 1), (200, 64, 20), (200, 20, 64), (72, 7, 5), (100, 3, 40), (33, 16, 4), (36, 32, 16), (256, 16, 16), (200, 20, 20), (64, 4, 4), (240, 4, 1), (256, 1, 1),
+          (272, 7, 1), (496, 64, 1), (512, 16, 1))
 REBLOCK = {f"{hb}_{bo}_{bn}": custom(num_layers=2, num_kv_heads=4, head_dim=hb, elem_bytes=1, old_block_size=bo,
                                      new_block_size=bn, num_seqs=4, length_law=("uniform", 1, 150), old_topo=(2, 1),
                                      new_topo=(4, 1)) for hb, bo, bn in BLOCKS}
@@ -51,16 +52,18 @@ def test_model_reblock(name):
 
 def test_dispatch_is_reached():
     """The cases take every kind of word and every shape of a wave, packed, unpacked and local."""
-    seen, local = set(), set()
+    seen, local, tokens = set(), set(), set()
     for w in list(CASES.values()) + list(REBLOCK.values()):
         m = km.Migration(w, synthkv.make_inputs(w), data=False)
         for pack, ranks, run in ((True, m.old, m.pack_launches), (False, m.new, m.unpack_launches)):
             for r in range(ranks.tp * ranks.pp):
                 seen |= {(pack, x.args["shape"], x.args["vec"]) for x in run(r, 0, m.L) if x.kernel == "copy_runs"}
         for r in range(min(m.old.tp, m.new.tp)):
-            local |= {(x.args["n"], x.args["m"], x.args["vec"]) for x in m.local_launches(r, 0, m.L)}
+            local |= {(x.args["n"], x.args["m"], x.args["vec"]) for x in m.local_launches(r, 0, m.L)
+                      if x.kernel == "copy_local"}
+            tokens |= {i.row_bytes for x in m.local_launches(r, 0, m.L) if x.kernel == "copy_local_tokens" for i in x.args["items"]}
     assert seen >= {(True, "cut", 8), (True, "cut", 0), (False, "rows", 8), (False, "rows", 0), (False, "cut", 0)}
-    assert {v for _, _, v in local} == {16, 8, 0}
+    assert {v for _, _, v in local} == {16, 8, 0} and tokens == {256, 272, 496}
     assert {(n, m) for n, m, _ in local} >= {(0, 1), (1, 1), (1, 2), (2, 1), (2, 2), (4, 1), (4, 0), (1, 0), (2, 0)}
 
 
