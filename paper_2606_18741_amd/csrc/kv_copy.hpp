@@ -1,4 +1,4 @@
-// The pack / unpack copy kernel (copy_runs) and the NHD local copies (copy_local, copy_local_tokens).
+// The pack / unpack copy kernel (copy_runs) and the NHD local copies (copy_local, copy_local_rows).
 // Included by migrate.hip only (one translation unit holds every kernel).
 #pragma once
 
@@ -121,8 +121,9 @@ struct LocalArgs {
     int64_t old_block_stride, new_block_stride;
     uint32_t n_new_desc, n_old_desc;
     uint32_t old_row_stride, new_row_stride;
-    uint32_t old_block_size;
+    uint32_t old_block_size, new_block_size;
     uint32_t bo_magic, bo_shift;  // fast division by the old block size
+    uint32_t bn_magic, bn_shift;  // and by the new one
     uint32_t xcd;                 // as in CopyArgs
     StampCheck check;
     LocalItem items[kMaxLocalItems];
@@ -294,36 +295,42 @@ __global__ __launch_bounds__(kMaxRunThreads) void copy_local(const LocalArgs arg
         if (left[k]) word[k].store(dst[k], left[k]);
 }
 
-// The same for new blocks of one token, of aligned rows of 256 to 511 bytes: a wave of copy_local meets four blocks, whose
-// look-ups cost more than its 1 KiB.  Here it takes 4 KiB: each lane looks up one of its rows, and the lanes that
-// move a row's vectors get its two addresses from that lane.  Bound by HBM and the look-ups' latency.  Measured on MI355X (us,
-// rows resolved into LDS / copy_local / so), 256-byte rows: blocks of 16 to 1, 1.8 GB, 377 / 410 / 372; 0.45 GB 120 / 126 / 118;
-// blocks of 1 122 / 133 / 123.  One wave to a workgroup instead of four 391, two vectors a lane 416; rows of 64 bytes
-// are faster by copy_local (183 / 194), and so are rows of 512 (97).
-constexpr int kTokenThreads = 256, kTokenVectors = 4;
-constexpr uint32_t kTokenMinRow = 256, kTokenEndRow = 512;
+// The same for aligned rows of 64 bytes and more in new blocks of less than 1 KiB: a wave of copy_local meets three blocks or
+// more, whose look-ups cost more than its 1 KiB.  Here it takes 4 KiB: each lane looks up one of its rows, and the
+// lanes that move a row's vectors get its two addresses from that lane.  Bound by HBM and the look-ups' latency.  Measured on
+// MI355X (us, rows resolved into LDS / copy_local / so): 64-byte rows in blocks of 5 535 / 596 / 515, of 12 465 / 502 / 435, of 128
+// bytes in blocks of 5 467 / 502 / 437, blocks of 16 to 6 459 / 512 / 432, 256 bytes, blocks of 16 to 1 378 / 410 / 360.  One
+// wave to a workgroup instead of four 391 in the last.  Not where a wave of copy_local meets two blocks at most (256 bytes in blocks of
+// 2 200 / 205, 512 bytes in blocks of 1 97 / 105), and not where rows end inside lines that others go on in (64 of 128 bytes in blocks
+// of 4 294 / 266 / 307, of 1 186 / 183 / 218).
+constexpr int kLookupThreads = 256, kLookupVectors = 4;
+constexpr uint32_t kLookupMinRow = 64;   // so that a wave has no more rows than lanes
 
-__global__ __launch_bounds__(kMaxRunThreads) void copy_local_tokens(const LocalArgs args) {
-    constexpr int K = kTokenVectors;
+__global__ __launch_bounds__(kMaxRunThreads) void copy_local_rows(const LocalArgs args) {
+    constexpr int K = kLookupVectors;
     if (stale_descriptors(args.check)) return;
     const LocalItem& it = args.items[blockIdx.y];
     const uint32_t kv = blockIdx.z, lane = threadIdx.x & 63u, w0 = wave_first(args.xcd) * K;
-    const uint32_t vpr = it.vpu;
-    const uint32_t u0 = fast_div(w0, it.vpu_magic, it.vpu_shift), u = u0 + lane;
-    const uint32_t end = min(fast_div(w0 + 64 * K - 1, it.vpu_magic, it.vpu_shift), args.n_new_desc - 1);   // the last one
+    const uint32_t vpr = it.row_bytes / kVecBytes;
+    // rows of all blocks are numbered one after another; the wave's first one, its last and the lane's
+    const uint32_t g0 = fast_div(w0, it.vpr_magic, it.vpr_shift);
+    const uint32_t end = min(fast_div(w0 + 64 * K - 1, it.vpr_magic, it.vpr_shift), args.n_new_desc * args.new_block_size - 1);
+    const uint32_t g = min(g0 + lane, end);
+    const uint32_t u = fast_div(g, args.bn_magic, args.bn_shift), row = g - u * args.new_block_size;
     const LocalUnit<1> x = load_local_unit<1>(args, reinterpret_cast<const Int4*>(args.new_desc),
                                               reinterpret_cast<const Int4*>(args.old_desc), args.tok_off,
-                                              args.old_blk_off, min(u, end), 0);
+                                              args.old_blk_off, u, row);
     uint64_t src = 0, dst = 0;
-    if (u <= end && x.n > 0) {
+    if (g0 + lane <= end && row < static_cast<uint32_t>(x.n)) {
         int32_t block;
         uint32_t slot;
-        if (find_source(args, x, 0, &block, &slot)) {
+        if (find_source(args, x, row, &block, &slot)) {
             src = (kv ? it.src_v : it.src_k) +
                   static_cast<uint64_t>(static_cast<uint32_t>(block)) * static_cast<uint64_t>(args.old_block_stride) +
                   static_cast<uint64_t>(slot) * args.old_row_stride;
             dst = (kv ? it.dst_v : it.dst_k) +
-                  static_cast<uint64_t>(static_cast<uint32_t>(x.block)) * static_cast<uint64_t>(args.new_block_stride);
+                  static_cast<uint64_t>(static_cast<uint32_t>(x.block)) * static_cast<uint64_t>(args.new_block_stride) +
+                  static_cast<uint64_t>(row) * args.new_row_stride;
         } else {
             *args.flag = kFlagTables;
         }
@@ -333,10 +340,10 @@ __global__ __launch_bounds__(kMaxRunThreads) void copy_local_tokens(const LocalA
     bool on[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const uint32_t w = w0 + k * 64 + lane, t = fast_div(w, it.vpu_magic, it.vpu_shift);
+        const uint32_t w = w0 + k * 64 + lane, t = fast_div(w, it.vpr_magic, it.vpr_shift);
         const uint32_t off = (w - t * vpr) * kVecBytes;
-        const uint64_t from = __shfl(src, static_cast<int>(t - u0), 64);
-        to[k] = __shfl(dst, static_cast<int>(t - u0), 64) + off;
+        const uint64_t from = __shfl(src, static_cast<int>(t - g0), 64);
+        to[k] = __shfl(dst, static_cast<int>(t - g0), 64) + off;
         on[k] = from != 0;
         if (on[k]) val[k] = __builtin_nontemporal_load((const REMP_GLOBAL Vec16*)(from + off));
     }

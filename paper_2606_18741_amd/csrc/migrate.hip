@@ -1087,11 +1087,18 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
     const uint32_t word = vec ? vec : kVecBytes;   // bytes of a word
     const auto vectors = [&](uint32_t row) { return static_cast<uint64_t>(bn) * ((row + word - 1) / word); };
     const uint64_t max_vpu = vectors(max_row);
-    const bool tokens = bn == 1 && !odd && min_row >= kTokenMinRow && max_row < kTokenEndRow;   // copy_local_tokens
-    const uint32_t words = tokens ? kTokenVectors : vec != 8 ? 1 : max_vpu >= 64 * kLocalWords ? kLocalWords : 2;   // of a lane
+    uint32_t xcd = 0;
+    bool lookup = !odd && min_row >= kLookupMinRow;   // copy_local_rows: where waves of copy_local meet more than two blocks
+    for (const HostLocal& it : items) {
+        xcd |= shares_lines(it.row_bytes, orow, odd) | shares_lines(it.row_bytes, nrow, odd);
+        const int u = units_per_wave(static_cast<uint32_t>(vectors(it.row_bytes)));
+        lookup &= u != 1 && u != 2;
+    }
+    lookup &= !xcd;
+    const uint32_t words = lookup ? kLookupVectors : vec != 8 ? 1 : max_vpu >= 64 * kLocalWords ? kLocalWords : 2;   // of a lane
     if (bn > kMaxLocalRows) return fail(REMP_E_UNSUPPORTED, "new block size above the local-copy row limit");
     if (max_vpu >= kMaxUnitVectors) return fail(REMP_E_UNSUPPORTED, "a block of one slice exceeds 2^31 vectors");
-    const int threads = run_threads(p, tokens ? kTokenThreads : kRunThreads);
+    const int threads = run_threads(p, lookup ? kLookupThreads : kRunThreads);
 
     LocalArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -1108,9 +1115,12 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
     const FastDiv fo = make_fastdiv(static_cast<uint32_t>(bo));
     a.bo_magic = fo.magic;
     a.bo_shift = fo.shift;
+    const FastDiv fn = make_fastdiv(static_cast<uint32_t>(bn));
+    a.new_block_size = static_cast<uint32_t>(bn);
+    a.bn_magic = fn.magic;
+    a.bn_shift = fn.shift;
     a.check = check;
-    for (const HostLocal& it : items)
-        a.xcd |= shares_lines(it.row_bytes, orow, odd) | shares_lines(it.row_bytes, nrow, odd);
+    a.xcd = xcd;
     const BlockDesc* desc = reinterpret_cast<const BlockDesc*>(ws + L.sorted_new);
     const uint32_t per_launch = units_per_launch(n_desc, max_vpu, 1);
     if (g_trace_start) {
@@ -1147,9 +1157,9 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
             a.n_new_desc = static_cast<uint32_t>(std::min<int64_t>(per_launch, n_desc - d0));
             const uint64_t wgs = (a.n_new_desc * max_vpu + threads * words - 1) / (threads * words);
             const dim3 grid(static_cast<uint32_t>(a.xcd ? xcd_grid(wgs) : wgs), static_cast<uint32_t>(cnt), 2);
-            if (tokens) {
-                hipLaunchKernelGGL(copy_local_tokens, grid, dim3(threads), 0, stream, a);
-                if (remp_status st = hip_check(hipGetLastError(), "copy_local_tokens launch")) return st;
+            if (lookup) {
+                hipLaunchKernelGGL(copy_local_rows, grid, dim3(threads), 0, stream, a);
+                if (remp_status st = hip_check(hipGetLastError(), "copy_local_rows launch")) return st;
                 continue;
             }
             switch (n) {

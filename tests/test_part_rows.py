@@ -32,11 +32,16 @@ CASES = {f"{hb}_{bs}{'_back' if back else ''}": _parts(hb, bs, back=back) for hb
 
 # (head bytes, old block, new block): rows from one old block, two, many; waves that meet one new block to many
 BLOCKS = ((256, 64, 20), (256, 16, 1), (256, 1, 16), (512, 3, 64), (1024, 16, 128), (64, 16, 64), (64, 64, 16), (64, 2, 2),
-          (16, 8, 8), (16, 16, 1), (16, 16, 64), (16, 16, 96), (128, 1, 1), (200, 64, 20), (200, 20, 64), (72, 7, 5), (100, 3, 40), (33, 16, 4), (36, 32, 16), (256, 16, 16), (200, 20, 20), (64, 4, 4), (240, 4, 1), (256, 1, 1),
-          (272, 7, 1), (496, 64, 1), (512, 16, 1))
+          (16, 8, 8), (16, 16, 1), (16, 16, 64), (16, 16, 96), (128, 1, 1), (200, 64, 20), (200, 20, 64), (72, 7, 5), (100, 3, 40), (33, 16, 4), (36, 32, 16), (256, 16, 16), (200, 20, 20), (64, 4, 4), (256, 1, 1),
+          (272, 7, 1), (496, 64, 1), (512, 16, 1), (128, 16, 6), (128, 16, 8), (256, 2, 3), (384, 3, 2))
+# rows of whole ranks: look-ups by row (64 to 1008 bytes a block, 4 to 63 vectors a row), and rows too short for it
+WHOLE = ((64, 1, 1), (64, 5, 5), (64, 12, 15), (80, 8, 8), (144, 16, 4), (336, 3, 3), (1008, 2, 1), (48, 16, 16), (1024, 1, 1))
 REBLOCK = {f"{hb}_{bo}_{bn}": custom(num_layers=2, num_kv_heads=4, head_dim=hb, elem_bytes=1, old_block_size=bo,
                                      new_block_size=bn, num_seqs=4, length_law=("uniform", 1, 150), old_topo=(2, 1),
                                      new_topo=(4, 1)) for hb, bo, bn in BLOCKS}
+REBLOCK.update({f"whole_{hb}_{bo}_{bn}": custom(num_layers=2, num_kv_heads=2, head_dim=hb, elem_bytes=1, old_block_size=bo,
+                                                new_block_size=bn, num_seqs=4, length_law=("uniform", 1, 150),
+                                                old_topo=(2, 1), new_topo=(2, 1)) for hb, bo, bn in WHOLE})
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -52,7 +57,7 @@ def test_model_reblock(name):
 
 def test_dispatch_is_reached():
     """The cases take every kind of word and every shape of a wave, packed, unpacked and local."""
-    seen, local, tokens = set(), set(), set()
+    seen, local, rows = set(), set(), set()
     for w in list(CASES.values()) + list(REBLOCK.values()):
         m = km.Migration(w, synthkv.make_inputs(w), data=False)
         for pack, ranks, run in ((True, m.old, m.pack_launches), (False, m.new, m.unpack_launches)):
@@ -61,9 +66,9 @@ def test_dispatch_is_reached():
         for r in range(min(m.old.tp, m.new.tp)):
             local |= {(x.args["n"], x.args["m"], x.args["vec"]) for x in m.local_launches(r, 0, m.L)
                       if x.kernel == "copy_local"}
-            tokens |= {i.row_bytes for x in m.local_launches(r, 0, m.L) if x.kernel == "copy_local_tokens" for i in x.args["items"]}
+            rows |= {i.row_bytes for x in m.local_launches(r, 0, m.L) if x.kernel == "copy_local_rows" for i in x.args["items"]}
     assert seen >= {(True, "cut", 8), (True, "cut", 0), (False, "rows", 8), (False, "rows", 0), (False, "cut", 0)}
-    assert {v for _, _, v in local} == {16, 8, 0} and tokens == {256, 272, 496}
+    assert {v for _, _, v in local} == {16, 8, 0} and rows == {64, 80, 128, 144, 256, 384}
     assert {(n, m) for n, m, _ in local} >= {(0, 1), (1, 1), (1, 2), (2, 1), (2, 2), (4, 1), (4, 0), (1, 0), (2, 0)}
 
 
