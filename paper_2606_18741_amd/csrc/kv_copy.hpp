@@ -301,10 +301,12 @@ __global__ __launch_bounds__(kMaxRunThreads) void copy_local(const LocalArgs arg
 // MI355X (us, rows resolved into LDS / copy_local / so): 64-byte rows in blocks of 5 535 / 596 / 515, of 12 465 / 502 / 435, of 128
 // bytes in blocks of 5 467 / 502 / 437, blocks of 16 to 6 459 / 512 / 432, 256 bytes, blocks of 16 to 1 378 / 410 / 360.  One
 // wave to a workgroup instead of four 391 in the last.  Not where a wave of copy_local meets two blocks at most (256 bytes in blocks of
-// 2 200 / 205, 512 bytes in blocks of 1 97 / 105), and not where rows end inside lines that others go on in (64 of 128 bytes in blocks
-// of 4 294 / 266 / 307, of 1 186 / 183 / 218).
+// 2 200 / 205, 512 bytes in blocks of 1 97 / 105), not where rows end inside lines that others go on in (64 of 128 bytes in blocks
+// of 4 294 / 266 / 307, of 1 186 / 183 / 218), and not in blocks that end inside 64 bytes, or are no more (80 bytes 928 / 876 / 956, 336
+// bytes 610 / 551 / 658, 64 bytes 784 / 813 / 838).
 constexpr int kLookupThreads = 256, kLookupVectors = 4;
-constexpr uint32_t kLookupMinRow = 64;   // so that a wave has no more rows than lanes
+constexpr uint32_t kLookupMinRow = 64;     // so that a wave has no more rows than lanes
+constexpr uint32_t kLookupMinBlock = 128;
 
 __global__ __launch_bounds__(kMaxRunThreads) void copy_local_rows(const LocalArgs args) {
     constexpr int K = kLookupVectors;

@@ -175,11 +175,12 @@ static int run_threads(const remp_kv_plan_t& p, int builtin) {
 // Workgroups of a grid whose kernel numbers them by xcd_position.
 static uint64_t xcd_grid(uint64_t wgs) { return (wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun); }
 
-// Whether rows of `row` bytes, `stride` apart, end inside lines of the L2 (128 bytes) that other rows or shares go on
-// in, or `odd` addresses make them: then the workgroups are numbered by xcd_position (MI355X, shares of 400 bytes
-// 1317 -> 1262 us, of 160 362 -> 349; where no line is shared it costs 0.7-1.5%).
-static uint32_t shares_lines(uint64_t row, uint64_t stride, bool odd) {
-    return odd || (row != stride && (row | stride) % 128 != 0);
+// Whether rows of `row` bytes, `stride` apart, or blocks of `block` bytes of whole rows, end inside lines of the L2 (128 bytes) that
+// others go on in, or `odd` addresses make them: then the workgroups are numbered by xcd_position (MI355X, us, without / with: shares of
+// 400 bytes 1317 / 1262, of 160 362 / 349; whole rows unpacked, blocks of 336 bytes 664 / 500, of 528 610 / 481, of 320 470 / 453, 1008
+// bytes copied locally 533 / 450; where no line is shared it costs 0.7-1.5%).
+static uint32_t shares_lines(uint64_t row, uint64_t stride, uint64_t block, bool odd) {
+    return odd || (row == stride ? block : row | stride) % 128 != 0;
 }
 
 // Units of `vpu` vectors that one launch can number: a dispatch counts its work-items in 32 bits, and `shares`
@@ -274,7 +275,8 @@ static remp_status launch_copy(const remp_kv_plan_t& p, const std::vector<HostSl
     a.total_tokens = p.total_tokens;
     a.row_stride = static_cast<uint32_t>(row_stride);
     a.check = check;
-    for (const HostSlice& s : slices) a.xcd |= shares_lines(s.row_bytes, a.row_stride, odd);
+    for (const HostSlice& s : slices)
+        a.xcd |= shares_lines(s.row_bytes, a.row_stride, static_cast<uint64_t>(bs) * s.row_bytes, odd);
     const BlockDesc* desc = reinterpret_cast<const BlockDesc*>(ws + desc_off);
     const uint32_t per_launch = units_per_launch(n_desc, max_vpu, 1);
     if (g_trace_start) {
@@ -648,7 +650,7 @@ static remp_status launch_rows(const remp_kv_plan_t& p, const std::vector<HostSl
     const FastDiv fp = make_fastdiv(seg_bytes);
     a.piece_magic = fp.magic;
     a.piece_shift = fp.shift;
-    a.xcd = order == kByRow ? shares_lines(seg_bytes, row_stride, odd) : 0;
+    a.xcd = order == kByRow ? shares_lines(seg_bytes, row_stride, 0, odd) : 0;
     const bool wave = order == kByShare || pieces;
     const int threads = wave ? 64 : run_threads(p, PACK || odd ? kRowsPackThreads : kRunThreads);
     const uint32_t shares = order == kByShare || (pieces && PACK) ? nseg : 1;
@@ -1088,13 +1090,16 @@ static remp_status launch_local(const remp_kv_plan_t& p, const std::vector<HostL
     const auto vectors = [&](uint32_t row) { return static_cast<uint64_t>(bn) * ((row + word - 1) / word); };
     const uint64_t max_vpu = vectors(max_row);
     uint32_t xcd = 0;
-    bool lookup = !odd && min_row >= kLookupMinRow;   // copy_local_rows: where waves of copy_local meet more than two blocks
+    // copy_local_rows: where waves of copy_local meet more than two blocks
+    bool lookup = !odd && min_row >= kLookupMinRow && static_cast<uint64_t>(bn) * min_row >= kLookupMinBlock &&
+                  static_cast<uint64_t>(bn) * nrow % 64 == 0;
     for (const HostLocal& it : items) {
-        xcd |= shares_lines(it.row_bytes, orow, odd) | shares_lines(it.row_bytes, nrow, odd);
+        const uint32_t rows = shares_lines(it.row_bytes, orow, 0, odd) | shares_lines(it.row_bytes, nrow, 0, odd);
         const int u = units_per_wave(static_cast<uint32_t>(vectors(it.row_bytes)));
-        lookup &= u != 1 && u != 2;
+        lookup &= !rows && u != 1 && u != 2;
+        xcd |= rows | shares_lines(it.row_bytes, nrow, static_cast<uint64_t>(bn) * nrow, odd);
     }
-    lookup &= !xcd;
+    if (lookup) xcd = 0;
     const uint32_t words = lookup ? kLookupVectors : vec != 8 ? 1 : max_vpu >= 64 * kLocalWords ? kLocalWords : 2;   // of a lane
     if (bn > kMaxLocalRows) return fail(REMP_E_UNSUPPORTED, "new block size above the local-copy row limit");
     if (max_vpu >= kMaxUnitVectors) return fail(REMP_E_UNSUPPORTED, "a block of one slice exceeds 2^31 vectors");
