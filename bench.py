@@ -165,10 +165,15 @@ def copy_calibration(gib: float) -> None:
                       "ms_per_copy": round(ms, 4), "copy_GBps_read_plus_write": round(2 * n / ms / 1e6, 1)}))
 
 
+# Tokens a block of the calibration pool: 64 KiB blocks, since each XCD reads every descriptor (with 4 KiB blocks
+# they were 6% of what the pack fetched, which the known bytes do not hold).
+CALIBRATION_BLOCK = 256
+
+
 def _calibration_bytes(gib: float) -> int:
-    """Bytes the library-calibration pack reads (and writes): K and V of a pool of `gib` GiB, 4 KiB blocks."""
-    nblk = int(gib * (1 << 30)) // (2 * 16 * 256)
-    return 2 * nblk * 16 * 256
+    """Bytes the library-calibration pack reads (and writes): K and V of a pool of `gib` GiB, 64 KiB blocks."""
+    nblk = int(gib * (1 << 30)) // (2 * CALIBRATION_BLOCK * 256)
+    return 2 * nblk * CALIBRATION_BLOCK * 256
 
 
 def library_calibration(gib: float) -> int:
@@ -182,7 +187,7 @@ def library_calibration(gib: float) -> int:
     import paper_2606_18741_amd as rk
     from paper_2606_18741_amd import torch_io as tio
 
-    bs, D = 16, 128
+    bs, D = CALIBRATION_BLOCK, 128
     row = D * 2
     nblk = int(gib * (1 << 30)) // (2 * bs * row)          # K and V pools together hold `gib` GiB
     T = nblk * bs
@@ -316,7 +321,7 @@ def summarize_trace(path: str) -> int:
     print("| kernel | calls | average (ms) | total (ms) |")
     print("|---|---|---|---|")
     for r in sorted(rows, key=lambda r: -float(r["TotalDurationNs"])):
-        name = r["Name"].replace("void ", "").replace("remp::", "").split("(")[0]
+        name = r["Name"].replace("void ", "").replace("remp::", "").replace("(RunShape)", "").split("(")[0]
         print(f"| `{name}` | {r['Calls']} | {float(r['AverageNs']) / 1e6:.4f} | {float(r['TotalDurationNs']) / 1e6:.3f} |")
     return 0
 
